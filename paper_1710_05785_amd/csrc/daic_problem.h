@@ -12,6 +12,7 @@
 
 namespace daic {
 struct SweepState;  // per-problem state of SWEEP scheduling (built on first use)
+struct SmallArgs;   // arguments of the one-workgroup runs of small problems
 }
 
 // ---------------------------------------------------------------------------
@@ -90,6 +91,7 @@ struct daic_problem {
   uint32_t* indeg = nullptr;     // in-degree of each vertex
   float* score = nullptr;        // selection multiplier of each vertex
   daic::SweepState* sweep = nullptr;
+  daic::SmallArgs* small = nullptr;  // whole runs in one workgroup: the layout (built on first use)
   void* cst = nullptr;           // constant c of the update function (fourth-condition check), or null
 };
 
@@ -149,6 +151,11 @@ daic_status dense_rounds_setup(daic_problem* p, const daic_run_opts* o, hipStrea
 void apply_run_opts(daic_problem* p, const daic_run_opts* o);
 // Fourth condition of Sec. 3.1 on the current state (needs the constant c).
 daic_status check_init(daic_problem* p, double tol, uint64_t* mismatches, hipStream_t s);
+// Runs of small problems: whether a run takes the one-workgroup form, and the
+// run itself (the control block's mirror h_ctl holds the result).
+bool small_applies(const daic_problem* p, const daic_run_opts* o);
+daic_status small_run(daic_problem* p, const daic_run_opts* o, hipStream_t s);
+void small_release(daic_problem* p);
 // SWEEP scheduling: the run loop, and the release of its per-problem state.
 daic_status sweep_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats, hipStream_t s);
 void sweep_release(daic_problem* p);

@@ -1036,6 +1036,27 @@ static double per_vertex_bytes(const daic_problem* p) {
   return b;
 }
 
+// The statistics and status of a run that ended (events ev0 and ev1 recorded,
+// the control block copied).
+static daic_status run_stats(daic_problem* p, bool learned, daic_stats* stats) {
+  float ms = 0.f;
+  DAIC_HIP(hipEventElapsedTime(&ms, p->ev0, p->ev1));
+  const Ctl& c = *p->h_ctl;
+  if (stats) {
+    stats->rounds = c.rounds;
+    stats->activations = c.activations;
+    stats->pushed_edges = c.pushed;
+    stats->final_residual = c.r;
+    stats->time_ms = ms;
+    stats->gteps = ms > 0 ? (double)c.pushed / (ms * 1e-3) / 1e9 : 0.0;
+    stats->alg_bytes = (double)c.pushed * per_edge_bytes(p) + (double)c.activations * per_vertex_bytes(p) +
+                       (double)c.rounds * (double)p->g->dev.n * (double)state_size(p->st) * 2.0;
+    stats->learned_fallbacks = learned ? c.l_fallbacks : 0;
+    stats->learned_exact_rounds = learned ? c.l_exact_rounds : 0;
+  }
+  return c.done ? DAIC_OK : DAIC_NOT_CONVERGED;
+}
+
 daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats) {
   if (!p) return fail(DAIC_E_INVALID, "problem is null");
   daic_status rc = check_opts(p, o);
@@ -1050,6 +1071,13 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
     if (rc) return rc;
   }
   if (o->sched == DAIC_SCHED_SWEEP) return sweep_run(p, o, stats, s);
+  if (small_applies(p, o)) {
+    DAIC_HIP(hipEventRecord(p->ev0, s));
+    rc = small_run(p, o, s);
+    if (rc) return rc;
+    p->a.last_upd = nullptr;
+    return run_stats(p, false, stats);
+  }
   Ops ops;
   if (!get_ops(p, &ops)) return fail(DAIC_E_UNSUPPORTED, "no kernel for this combination");
   const uint32_t K = o->rounds_per_check ? o->rounds_per_check : 1;
@@ -1166,22 +1194,7 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
   DAIC_HIP(hipEventRecord(p->ev1, s));
   DAIC_HIP(hipEventSynchronize(p->ev1));
   p->a.last_upd = nullptr;  // rounds of the other rules do not track updates
-  float ms = 0.f;
-  DAIC_HIP(hipEventElapsedTime(&ms, p->ev0, p->ev1));
-  const Ctl& c = *p->h_ctl;
-  if (stats) {
-    stats->rounds = c.rounds;
-    stats->activations = c.activations;
-    stats->pushed_edges = c.pushed;
-    stats->final_residual = c.r;
-    stats->time_ms = ms;
-    stats->gteps = ms > 0 ? (double)c.pushed / (ms * 1e-3) / 1e9 : 0.0;
-    stats->alg_bytes = (double)c.pushed * per_edge_bytes(p) + (double)c.activations * per_vertex_bytes(p) +
-                       (double)c.rounds * (double)n * (double)state_size(p->st) * 2.0;
-    stats->learned_fallbacks = learned ? c.l_fallbacks : 0;
-    stats->learned_exact_rounds = learned ? c.l_exact_rounds : 0;
-  }
-  return c.done ? DAIC_OK : DAIC_NOT_CONVERGED;
+  return run_stats(p, learned, stats);
 }
 
 daic_status daic_problem_set_init_device(daic_problem* p, const void* d_v0, const void* d_dv1, void* hip_stream) {
@@ -1512,6 +1525,7 @@ daic_status daic_problem_get(const daic_problem* p, void* v_out, void* dv_out) {
 void daic_problem_destroy(daic_problem* p) {
   if (!p) return;
   sweep_release(p);
+  small_release(p);
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   if (p->graph) (void)hipGraphDestroy(p->graph);
   if (p->exec_fused) (void)hipGraphExecDestroy(p->exec_fused);
