@@ -30,7 +30,7 @@
 namespace daic {
 
 constexpr int kR = 64;                 // right-hand sides per vertex (padded)
-constexpr uint32_t kBChunk = 1024;     // in-edges per pull item
+constexpr uint32_t kBChunk = 1024;     // in-edges per pull item (at most)
 constexpr uint32_t kPushChunk = 256;   // out-edges per push item
 constexpr uint32_t kResChunk = 4096;   // at most this many vertices per residual item
 constexpr uint32_t kItemWork = 32768;  // and about this much work (in-edges + kVertexWork per vertex)
@@ -40,6 +40,15 @@ constexpr uint32_t kVertexWork = 4;
 constexpr uint32_t kSwResChunk = 1024;
 constexpr uint32_t kSwItemWork = 8192;
 constexpr uint32_t kSwHubChunk = 256;
+// A batch that those sizes would cut into few items gets smaller ones, so
+// that about kItemsWanted workgroups (eight for each of the 256 CUs) share a
+// round: 120,000 vertices and 960,000 edges made 30 items and a round of
+// 0.61 ms of two kernels that left most CUs idle, against 0.13 ms in 2,100
+// items. At least four passes of a workgroup's 16 vertices per item, and hub
+// chunks of at least 64 in-edges.
+constexpr uint32_t kItemsWanted = 2048;
+constexpr uint32_t kItemVertsMin = 64;
+constexpr uint32_t kHubChunkMin = 64;
 constexpr uint32_t kHubDeg = 64;       // default in-degree above which a target is a hub
 
 // Round modes: 0 = sparse round (claim, push, residual); 1 = the claim that
@@ -106,8 +115,7 @@ struct BArgs {
   uint64_t* part_fm;
   double* inst_r;             // [G][64] residual per instance
   uint64_t pull_min;          // dense phase when union pending >= pull_min
-  // per graph: item tickets and the sums of its retired items
-  uint32_t* g_ticket;
+  // per graph: the sums of its retired items
   uint32_t* g_flag;
   uint64_t* g_pend;
   uint64_t* g_act;
@@ -299,8 +307,18 @@ __device__ void retire_graph(const BArgs& a, uint32_t g, int kind, int count_rou
   const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
   const uint32_t k0 = a.g_first_item[g], k1 = a.g_first_item[g + 1];
   double r = 0.0;
-  for (uint32_t k = k0 + wave; k < k1; k += 4)
-    r += __hip_atomic_load(&a.part_r[(uint64_t)k * kR + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // sixteen items' partials in flight, added in item order (one load at a
+  // time is a round trip per item: 24 us for 170 items a graph, 9 us so)
+  for (uint32_t k = k0 + wave; k < k1; k += 64) {
+    double x[16];
+#pragma unroll
+    for (uint32_t u = 0; u < 16; ++u)
+      x[u] = __hip_atomic_load(&a.part_r[(uint64_t)min(k + 4 * u, k1 - 1) * kR + lane], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (uint32_t u = 0; u < 16; ++u)
+      if (k + 4 * u < k1) r += x[u];
+  }
   s_r[wave][lane] = r;
   uint64_t pend = 0, act = 0, msg = 0;
   for (uint32_t k = k0 + threadIdx.x; k < k1; k += 256) {
@@ -338,7 +356,6 @@ __device__ void retire_graph(const BArgs& a, uint32_t g, int kind, int count_rou
       a.g_pend[g] = pend;
       a.g_act[g] = act;
       a.g_msg[g] = msg;
-      a.g_ticket[g] = 0;
     }
   }
   __syncthreads();
@@ -382,23 +399,15 @@ __device__ void retire_graph(const BArgs& a, uint32_t g, int kind, int count_rou
   }
 }
 
-__device__ void retire_item(const BArgs& a, uint32_t g, int kind, int count_round) {
-  __shared__ uint32_t s_last;
-  __threadfence();  // this block's partials are visible before its ticket
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t nit = a.g_first_item[g + 1] - a.g_first_item[g];
-    s_last = atomicAdd(&a.g_ticket[g], 1u) == nit - 1;
-  }
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  retire_graph(a, g, kind, count_round);
+// Retirement of a pass, after it (its kernel only stores partials: a fence
+// per item in a kernel that keeps dirtying L2 would write the L2 back each
+// time, and the items' tickets would take turns: the residual of 2,100 items
+// took 216 us with both): one block per graph.
+__global__ __launch_bounds__(256) void k_bretire_sparse(BArgs a, int count_round) {
+  if (bhalted(a.ctl) || a.ctl->mode != 0) return;  // as k_bresidual
+  retire_graph(a, blockIdx.x, 0, count_round);
 }
 
-// Retirement of the fused dense pass, after it (its kernel only stores
-// partials: a fence per item in a kernel that keeps dirtying L2 would write
-// the L2 back each time): one block per graph.
 __global__ __launch_bounds__(256) void k_bretire_dense(BArgs a, int final_pass) {
   BCtl* ctl = a.ctl;
   if (!final_pass && (bhalted(ctl) || ctl->mode != 2)) return;  // as k_bfused
@@ -459,7 +468,7 @@ __global__ __launch_bounds__(256) void k_bresidual(BArgs a, int count_round) {
     a.part_fa[it] = 0;
     a.part_fm[it] = 0;
   }
-  retire_item(a, a.rg[it], 0, count_round);
+  // retired after the kernel: k_bretire_sparse
 }
 
 // Dense phase, hub targets (in-degree > hub_deg): one item per (target, chunk
@@ -467,25 +476,39 @@ __global__ __launch_bounds__(256) void k_bresidual(BArgs a, int count_round) {
 // the instances whose messages are not yet all delivered; atomics where a
 // target has several chunks.
 // Sum over in-edges [beg, end) of the message-base vectors (times the edge
-// weight under EDGE_SCALE), four gathers in flight per lane.
+// weight under EDGE_SCALE), four gathers in flight per lane, with the next
+// four sources (and weights) on their way while they arrive.
 template <int W, bool WGT>
 __device__ __forceinline__ void bgather(const BArgs& a, const float* mu_in, uint32_t beg, uint32_t end, uint32_t r0,
                                         float (&acc)[W]) {
   uint32_t p = beg;
-  for (; p + 3 < end; p += 4) {
-    const uint32_t s0 = a.srcT[p], s1 = a.srcT[p + 1], s2 = a.srcT[p + 2], s3 = a.srcT[p + 3];
-    float x0[W], x1[W], x2[W], x3[W];
-    vload<W>(mu_in + (uint64_t)s0 * kR + r0, x0);
-    vload<W>(mu_in + (uint64_t)s1 * kR + r0, x1);
-    vload<W>(mu_in + (uint64_t)s2 * kR + r0, x2);
-    vload<W>(mu_in + (uint64_t)s3 * kR + r0, x3);
-    if constexpr (WGT) {
-      const float w0 = a.wT[p], w1 = a.wT[p + 1], w2 = a.wT[p + 2], w3 = a.wT[p + 3];
+  if (p + 3 < end) {
+    uint32_t sn[4];
+    float wn[4];
 #pragma unroll
-      for (int k = 0; k < W; ++k) acc[k] += (x0[k] * w0 + x1[k] * w1) + (x2[k] * w2 + x3[k] * w3);
-    } else {
+    for (int u = 0; u < 4; ++u) {
+      sn[u] = a.srcT[p + u];
+      if constexpr (WGT) wn[u] = a.wT[p + u];
+    }
+    for (; p + 3 < end; p += 4) {
+      float x[4][W], w[4];
 #pragma unroll
-      for (int k = 0; k < W; ++k) acc[k] += (x0[k] + x1[k]) + (x2[k] + x3[k]);
+      for (int u = 0; u < 4; ++u) {
+        vload<W>(mu_in + (uint64_t)sn[u] * kR + r0, x[u]);
+        if constexpr (WGT) w[u] = wn[u];
+      }
+      if (p + 7 < end) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          sn[u] = a.srcT[p + 4 + u];
+          if constexpr (WGT) wn[u] = a.wT[p + 4 + u];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        if constexpr (WGT) acc[k] += (x[0][k] * w[0] + x[1][k] * w[1]) + (x[2][k] * w[2] + x[3][k] * w[3]);
+        else acc[k] += (x[0][k] + x[1][k]) + (x[2][k] + x[3][k]);
+      }
     }
   }
   for (; p < end; ++p) {
@@ -908,14 +931,6 @@ __global__ void k_bto_sparse(BCtl* ctl) {
   ctl->ticket = 0;
 }
 
-// Item tickets of every graph and the graph ticket back to 0. A run stopped
-// between sweep rounds leaves some graphs' items of the interrupted sweep
-// counted; every run and every delivery starts from here.
-__global__ void k_breset_tickets(BArgs a) {
-  for (uint32_t g = threadIdx.x; g < a.G; g += blockDim.x) a.g_ticket[g] = 0;
-  if (threadIdx.x == 0) a.ctl->ticket = 0;
-}
-
 __global__ void k_bstats(BArgs a, uint32_t nblocks) {
   if (bhalted(a.ctl) || a.ctl->mode >= 2) return;
   uint64_t s = 0, m = 0;
@@ -1051,9 +1066,18 @@ struct daic_batch {
   uint32_t sw_grid = 0;               // fused-pass blocks per sweep round
   std::vector<void*> sw_allocs;
   std::vector<uint32_t> xcd_of;       // XCD slot given to each graph
+  uint32_t item_verts = kResChunk, item_work = kItemWork;  // most vertices and work of an item
+  hipGraphExec_t exec_f = nullptr;    // fused dense rounds only
+  hipGraph_t graph_f = nullptr;
 };
 
 namespace daic {
+
+// The residual of a delivered state and the finish states that follow.
+static void enqueue_residual(daic_batch* b, hipStream_t s, int count_round) {
+  hipLaunchKernelGGL(k_bresidual, dim3(b->a.n_res), dim3(256), 0, s, b->a, count_round);
+  hipLaunchKernelGGL(k_bretire_sparse, dim3(b->a.G), dim3(256), 0, s, b->a, count_round);
+}
 
 template <int LPV, bool KAHAN>
 static void launch_claim(daic_batch* b, hipStream_t s) {
@@ -1115,8 +1139,7 @@ static void launch_sweep_deliver_w(daic_batch* b, hipStream_t s) {
   hipLaunchKernelGGL((k_bdeliver<16, WGT>), dim3(bgrid(as.N, 16)), dim3(256), 0, s, as);
   if (as.n_hub) hipLaunchKernelGGL((k_bdeliver_hub<16, WGT>), dim3(bgrid(as.n_hub, 16)), dim3(256), 0, s, as);
   hipLaunchKernelGGL(k_bto_sparse, dim3(1), dim3(1), 0, s, as.ctl);
-  hipLaunchKernelGGL(k_breset_tickets, dim3(1), dim3(256), 0, s, b->a);
-  hipLaunchKernelGGL(k_bresidual, dim3(b->a.n_res), dim3(256), 0, s, b->a, 0);
+  enqueue_residual(b, s, 0);
 }
 
 template <int LPV>
@@ -1151,6 +1174,7 @@ static void enqueue_push(daic_batch* b, hipStream_t s) {
 // XCD-interleaved order and its hub items longest first.
 static daic_status batch_sweep_setup(daic_batch* b, uint32_t P, hipStream_t s) {
   if (b->sw_P == P) return DAIC_OK;
+  const uint32_t hub_chunk = std::min(kSwHubChunk, b->a.hub_chunk);
   for (void* q : b->sw_allocs)
     if (q) (void)hipFree(q);
   b->sw_allocs.clear();
@@ -1200,7 +1224,8 @@ static daic_status batch_sweep_setup(daic_batch* b, uint32_t P, hipStream_t s) {
       for (uint64_t j = seg_lo; j < seg_hi; ++j) {
         const uint32_t deg = rt[j + 1] - rt[j];
         w += (deg > a.hub_deg ? 0 : deg) + kVertexWork;
-        if (j + 1 - lo >= kSwResChunk || w >= kSwItemWork || j + 1 == seg_hi) {
+        if (j + 1 - lo >= std::min(kSwResChunk, b->item_verts) || w >= std::min(kSwItemWork, b->item_work) ||
+            j + 1 == seg_hi) {
           rg.push_back(g);
           rlo.push_back(lo);
           rhi.push_back(j + 1);
@@ -1262,8 +1287,8 @@ static daic_status batch_sweep_setup(daic_batch* b, uint32_t P, hipStream_t s) {
     for (uint64_t t = 0; t < N; ++t) {
       const uint32_t deg = rt[t + 1] - rt[t];
       if (deg <= a.hub_deg) continue;
-      for (uint32_t c = 0; c * kSwHubChunk < deg; ++c)
-        per[blk[t]].push_back({std::min(kSwHubChunk, deg - c * kSwHubChunk), (t << 32) | c});
+      for (uint32_t c = 0; c * hub_chunk < deg; ++c)
+        per[blk[t]].push_back({std::min(hub_chunk, deg - c * hub_chunk), (t << 32) | c});
     }
     for (uint32_t c = 0; c < P; ++c) {
       std::stable_sort(per[c].begin(), per[c].end(), [](const auto& x, const auto& y) { return x.first > y.first; });
@@ -1306,7 +1331,7 @@ static daic_status batch_sweep_setup(daic_batch* b, uint32_t P, hipStream_t s) {
 #undef SWGRAB
   as.n_res = (uint32_t)nres;
   as.n_hub = ht.size();
-  as.hub_chunk = kSwHubChunk;
+  as.hub_chunk = hub_chunk;
   as.sw_P = P;
   {
     uint32_t* d_inv = nullptr;
@@ -1334,7 +1359,7 @@ static void enqueue_round(daic_batch* b, hipStream_t s) {
   enqueue_claim(b, s);
   enqueue_push(b, s);
   enqueue_dense(b, s, 0);
-  hipLaunchKernelGGL(k_bresidual, dim3(b->a.n_res), dim3(256), 0, s, b->a, 1);
+  enqueue_residual(b, s, 1);
 }
 
 }  // namespace daic
@@ -1347,6 +1372,8 @@ void daic_batch_destroy(daic_batch* b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->exec_sw) (void)hipGraphExecDestroy(b->exec_sw);
   if (b->graph_sw) (void)hipGraphDestroy(b->graph_sw);
+  if (b->exec_f) (void)hipGraphExecDestroy(b->exec_f);
+  if (b->graph_f) (void)hipGraphDestroy(b->graph_f);
   for (void* q : b->allocs)
     if (q) (void)hipFree(q);
   for (void* q : b->sw_allocs)
@@ -1474,20 +1501,32 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
   BGRAB(inst_r, double*, (size_t)n_graphs * kR * 8);
   std::vector<uint32_t> rt(N + 1);
   {
-    // hub items: targets with in-degree > hub_deg, chunks of kBChunk
+    // hub items: targets with in-degree > hub_deg, chunks of at most kBChunk
     // in-edges, longest first
     a.hub_deg = kHubDeg;
-    a.hub_chunk = kBChunk;
     if (const char* e = std::getenv("DAIC_HUB_DEG")) a.hub_deg = (uint32_t)std::max(1L, std::atol(e));
     DAIC_HIP(hipMemcpy(rt.data(), ug->pull.rowT, (N + 1) * 4, hipMemcpyDeviceToHost));
+    {
+      uint64_t hub = 0, work = 0;  // in-edges of the hub targets, work of the fused pass
+      for (uint64_t t = 0; t < N; ++t) {
+        const uint32_t deg = rt[t + 1] - rt[t];
+        if (deg > a.hub_deg) hub += deg;
+        work += (deg > a.hub_deg ? 0 : deg) + kVertexWork;
+      }
+      b->item_verts = (uint32_t)std::min<uint64_t>(kResChunk, std::max<uint64_t>(kItemVertsMin, N / kItemsWanted));
+      b->item_work = (uint32_t)std::min<uint64_t>(
+          kItemWork, std::max<uint64_t>(kItemVertsMin * kVertexWork, work / kItemsWanted));
+      a.hub_chunk = kHubChunkMin;  // a power of two; 16 chunks to a workgroup
+      while (a.hub_chunk < kBChunk && hub / a.hub_chunk > 16 * kItemsWanted) a.hub_chunk *= 2;
+    }
     std::vector<uint32_t> ht, hc;
     {
       std::vector<std::pair<uint32_t, uint64_t>> items;  // (length, target << 32 | chunk)
       for (uint64_t t = 0; t < N; ++t) {
         const uint32_t deg = rt[t + 1] - rt[t];
         if (deg <= a.hub_deg) continue;
-        for (uint32_t c = 0; c * kBChunk < deg; ++c)
-          items.push_back({std::min(kBChunk, deg - c * kBChunk), (t << 32) | c});
+        for (uint32_t c = 0; c * a.hub_chunk < deg; ++c)
+          items.push_back({std::min(a.hub_chunk, deg - c * a.hub_chunk), (t << 32) | c});
       }
       std::stable_sort(items.begin(), items.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
       for (auto& it : items) {
@@ -1518,8 +1557,8 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
     BGRAB(sc, const uint32_t*, sc.size() * 4);
     DAIC_HIP(hipMemcpy((void*)a.sv, sv.data(), sv.size() * 4, hipMemcpyHostToDevice));
     DAIC_HIP(hipMemcpy((void*)a.sc, sc.data(), sc.size() * 4, hipMemcpyHostToDevice));
-    // residual items: vertex ranges inside each graph, closed at kResChunk
-    // vertices or kItemWork work (in-edges pulled in the fused pass plus a
+    // residual items: vertex ranges inside each graph, closed at item_verts
+    // vertices or item_work work (in-edges pulled in the fused pass plus a
     // per-vertex share for the claim), whichever comes first, so that the
     // in-edge-heavy low ids of an RMAT graph do not form one long item
     std::vector<uint32_t> rg, gfi;
@@ -1530,7 +1569,7 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
       for (uint64_t j = b->voff[g]; j < b->voff[g + 1]; ++j) {
         const uint32_t deg = rt[j + 1] - rt[j];
         w += (deg > a.hub_deg ? 0 : deg) + kVertexWork;
-        if (j + 1 - lo >= kResChunk || w >= kItemWork || j + 1 == b->voff[g + 1]) {
+        if (j + 1 - lo >= b->item_verts || w >= b->item_work || j + 1 == b->voff[g + 1]) {
           rg.push_back(g);
           rlo.push_back(lo);
           rhi.push_back(j + 1);
@@ -1589,22 +1628,39 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
     BGRAB(part_fm, uint64_t*, (size_t)a.n_res * 8);
     // Fused-pass block order. Workgroups go to the 8 XCDs round-robin by
     // block index and each XCD has its own L2, so every graph is given to one
-    // XCD (largest graphs first, to the least loaded XCD by in-edges) and its
-    // items take that XCD's block slots.
+    // XCD and its items take that XCD's block slots; a graph of more than half
+    // an XCD's share of the work is cut into pieces of as much (a batch of a
+    // few graphs would leave XCDs idle). Heaviest first, to the least loaded.
     constexpr uint32_t kXcd = 8;
-    std::vector<uint64_t> gw(n_graphs, 0);
-    for (uint32_t g = 0; g < n_graphs; ++g) gw[g] = rt[b->voff[g + 1]] - rt[b->voff[g]] + (b->voff[g + 1] - b->voff[g]);
-    std::vector<uint32_t> gorder(n_graphs);
-    for (uint32_t g = 0; g < n_graphs; ++g) gorder[g] = g;
-    std::stable_sort(gorder.begin(), gorder.end(), [&](uint32_t x, uint32_t y) { return gw[x] > gw[y]; });
+    uint64_t work = 0;
+    for (uint64_t w : rw) work += w;
+    struct Piece {
+      uint64_t work;
+      uint32_t g, k0, k1;  // items [k0, k1) of graph g
+    };
+    std::vector<Piece> pieces;
+    const uint64_t most = std::max<uint64_t>(1, work / (2 * kXcd));
+    for (uint32_t g = 0; g < n_graphs; ++g) {
+      Piece p{0, g, gfi[g], gfi[g]};
+      for (uint32_t k = gfi[g]; k < gfi[g + 1]; ++k) {
+        if (p.k1 > p.k0 && p.work + rw[k] > most) {
+          pieces.push_back(p);
+          p = Piece{0, g, k, k};
+        }
+        p.work += rw[k];
+        p.k1 = k + 1;
+      }
+      pieces.push_back(p);
+    }
+    std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.work > y.work; });
     std::vector<std::vector<uint32_t>> bins(kXcd);
     std::vector<uint64_t> load(kXcd, 0);
     b->xcd_of.assign(n_graphs, 0);
-    for (uint32_t g : gorder) {
+    for (const Piece& p : pieces) {
       const uint32_t x = (uint32_t)(std::min_element(load.begin(), load.end()) - load.begin());
-      load[x] += gw[g];
-      b->xcd_of[g] = x;
-      for (uint32_t k = gfi[g]; k < gfi[g + 1]; ++k) bins[x].push_back(k);
+      load[x] += p.work;
+      b->xcd_of[p.g] = x;
+      for (uint32_t k = p.k0; k < p.k1; ++k) bins[x].push_back(k);
     }
     // heaviest items first within each XCD, so that the long ones start early
     for (auto& bn : bins)
@@ -1618,7 +1674,6 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
     BGRAB(item_order, const uint32_t*, order.size() * 4);
     DAIC_HIP(hipMemcpy((void*)a.item_order, order.data(), order.size() * 4, hipMemcpyHostToDevice));
   }
-  BGRAB(g_ticket, uint32_t*, (size_t)n_graphs * 4);
   BGRAB(g_flag, uint32_t*, (size_t)n_graphs * 4);
   BGRAB(g_pend, uint64_t*, (size_t)n_graphs * 8);
   BGRAB(g_act, uint64_t*, (size_t)n_graphs * 8);
@@ -1643,7 +1698,6 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
   DAIC_HIP(hipMemsetAsync(a.mu, 0, SV, s));
   DAIC_HIP(hipMemsetAsync(a.mu2, 0, SV, s));
   DAIC_HIP(hipMemsetAsync(a.active, 0, N, s));
-  DAIC_HIP(hipMemsetAsync(a.g_ticket, 0, (size_t)n_graphs * 4, s));
   DAIC_HIP(hipMemsetAsync(a.done, 0, (size_t)n_graphs * kR, s));
   hipLaunchKernelGGL(k_binit, dim3(1), dim3(1), 0, s, a.ctl, 0.0, ~0ull, 1u);
   DAIC_HIP(hipHostMalloc((void**)&b->h_ctl, sizeof(BCtl), hipHostMallocDefault));
@@ -1817,6 +1871,11 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
   // to that many rounds is a single graph launch
   constexpr uint32_t kBatchLaunchRounds = 128;
   const uint32_t K = o->rounds_per_check ? o->rounds_per_check : kBatchLaunchRounds;
+  // the rounds until the host sees the dense phase launch the kernels of
+  // every mode; the dense phase then has a graph of its own, without the four
+  // that would return at once (4-5 us each)
+  constexpr uint32_t kBatchOpenRounds = 8;
+  const uint32_t K_open = std::min(K, kBatchOpenRounds);
   const uint64_t max_rounds = o->max_rounds ? o->max_rounds : ~0ull;
   if (stats) std::memset(stats, 0, sizeof *stats);
   BArgs& a = b->a;
@@ -1830,8 +1889,7 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
   }
   const uint32_t dense = sweep ? 3u : 1u;
   hipLaunchKernelGGL(k_binit, dim3(1), dim3(1), 0, s, a.ctl, o->eps, max_rounds, dense);
-  hipLaunchKernelGGL(k_breset_tickets, dim3(1), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_bresidual, dim3(a.n_res), dim3(256), 0, s, a, 0);
+  enqueue_residual(b, s, 0);
   DAIC_HIP(hipEventRecord(b->ev0, s));
   const bool use_graph = std::getenv("DAIC_NO_GRAPH") == nullptr;
   if (use_graph && !(b->exec && b->exec_K == K && b->exec_stream == s && b->exec_dense == dense &&
@@ -1840,14 +1898,22 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
     if (b->graph) { (void)hipGraphDestroy(b->graph); b->graph = nullptr; }
     if (b->exec_sw) { (void)hipGraphExecDestroy(b->exec_sw); b->exec_sw = nullptr; }
     if (b->graph_sw) { (void)hipGraphDestroy(b->graph_sw); b->graph_sw = nullptr; }
-    b->exec_K = 0;  // no match until both captures below have succeeded
+    if (b->exec_f) { (void)hipGraphExecDestroy(b->exec_f); b->exec_f = nullptr; }
+    if (b->graph_f) { (void)hipGraphDestroy(b->graph_f); b->graph_f = nullptr; }
+    b->exec_K = 0;  // no match until every capture below has succeeded
     DAIC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    for (uint32_t r = 0; r < K; ++r) enqueue_round(b, s);
+    for (uint32_t r = 0; r < K_open; ++r) enqueue_round(b, s);
     hipGraph_t graph;
     DAIC_HIP(hipStreamEndCapture(s, &graph));
     b->graph = graph;
     DAIC_HIP(hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0));
-    if (sweep) {
+    if (!sweep) {
+      DAIC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+      for (uint32_t r = 0; r < K; ++r) enqueue_dense(b, s, 0);
+      DAIC_HIP(hipStreamEndCapture(s, &graph));
+      b->graph_f = graph;
+      DAIC_HIP(hipGraphInstantiate(&b->exec_f, graph, nullptr, nullptr, 0));
+    } else {
       DAIC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
       for (uint32_t r = 0; r < K; ++r) enqueue_sweep(b, s);
       DAIC_HIP(hipStreamEndCapture(s, &graph));
@@ -1863,12 +1929,13 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
   DAIC_HIP(hipMemcpyAsync(b->h_ctl, a.ctl, sizeof(BCtl), hipMemcpyDeviceToHost, s));
   DAIC_HIP(hipStreamSynchronize(s));
   for (;;) {
-    const bool sweep_now = sweep && b->h_ctl->mode == 3;
+    const bool sweep_now = sweep && b->h_ctl->mode == 3, dense_now = b->h_ctl->mode == 2;
     if (use_graph) {
-      DAIC_HIP(hipGraphLaunch(sweep_now ? b->exec_sw : b->exec, s));
+      DAIC_HIP(hipGraphLaunch(sweep_now ? b->exec_sw : dense_now ? b->exec_f : b->exec, s));
     } else {
       for (uint32_t r = 0; r < K; ++r) {
         if (sweep_now) enqueue_sweep(b, s);
+        else if (dense_now) enqueue_dense(b, s, 0);
         else enqueue_round(b, s);
       }
     }
@@ -1895,7 +1962,7 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
       else launch_sweep_deliver_w<false>(b, s);
     } else {
       hipLaunchKernelGGL(k_bto_sparse, dim3(1), dim3(1), 0, s, a.ctl);
-      hipLaunchKernelGGL(k_bresidual, dim3(a.n_res), dim3(256), 0, s, a, 0);
+      enqueue_residual(b, s, 0);
     }
     DAIC_HIP(hipMemcpyAsync(b->h_ctl, a.ctl, sizeof(BCtl), hipMemcpyDeviceToHost, s));
     DAIC_HIP(hipStreamSynchronize(s));
