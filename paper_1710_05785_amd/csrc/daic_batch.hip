@@ -26,6 +26,7 @@
 
 #include "daic_device.h"
 #include "daic_internal.h"
+#include "daic_stage.h"
 
 namespace daic {
 
@@ -1026,6 +1027,35 @@ __global__ void k_bgather_weights(const float* w, const uint32_t* eidT, uint64_t
   for (uint64_t p = i; p < m; p += st) wT[p] = w[eidT[p]];
 }
 
+// Elements [first, first + n) of a [vertex][R] array of doubles against the
+// [vertex][64] state (minus, or with the rounding taken by, the Kahan term).
+__global__ void k_bstage_in(const double* in, uint64_t first, uint64_t n, uint32_t R, float* a, float* c) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t at = (first + i) / R * kR + (first + i) % R;
+    const double x = in[i];
+    a[at] = (float)x;
+    if (c) c[at] = (float)((double)(float)x - x);
+  }
+}
+
+__global__ void k_bstage_out(const float* a, const float* c, uint64_t first, uint64_t n, uint32_t R, double* out) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t at = (first + i) / R * kR + (first + i) % R;
+    out[i] = c ? (double)a[at] - (double)c[at] : (double)a[at];
+  }
+}
+
+// Zeroes count elements of a graph's state and its instances' finish states.
+__global__ void k_bclear(uint64_t count, float* v, float* dv, float* c, uint8_t* done) {
+  const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (uint64_t i = i0; i < count; i += (uint64_t)gridDim.x * blockDim.x) {
+    v[i] = 0.0f;
+    dv[i] = 0.0f;
+    if (c) c[i] = 0.0f;
+  }
+  if (i0 < kR) done[i0] = 0;
+}
+
 static uint32_t bgrid(uint64_t count, uint32_t block = 256) {
   uint64_t g = (count + block - 1) / block;
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(g, 8192));
@@ -1041,6 +1071,7 @@ struct BTune {
 };
 
 struct daic_batch {
+  StageUser stage;
   uint32_t G = 0;
   std::vector<uint64_t> voff, n_of;   // per graph vertex offset and count
   std::vector<uint32_t> rhs;          // right-hand sides used per graph
@@ -1714,21 +1745,20 @@ daic_status daic_batch_set_init(daic_batch* b, uint32_t graph, const double* v0,
   const uint64_t n = b->n_of[graph], off = b->voff[graph];
   const uint32_t R = b->rhs[graph];
   if (n == 0) return DAIC_OK;
-  std::vector<float> tv(n * kR, 0.0f), td(n * kR, 0.0f), tc(n * kR, 0.0f);
-  for (uint64_t j = 0; j < n; ++j)
-    for (uint32_t r = 0; r < R; ++r) {
-      const double x = v0[j * R + r];
-      tv[j * kR + r] = (float)x;
-      tc[j * kR + r] = (float)((double)(float)x - x);
-      td[j * kR + r] = (float)dv1[j * R + r];
-    }
-  DAIC_HIP(hipMemcpy(b->a.v + off * kR, tv.data(), n * kR * 4, hipMemcpyHostToDevice));
-  DAIC_HIP(hipMemcpy(b->a.dv + off * kR, td.data(), n * kR * 4, hipMemcpyHostToDevice));
-  if (b->a.c) DAIC_HIP(hipMemcpy(b->a.c + off * kR, tc.data(), n * kR * 4, hipMemcpyHostToDevice));
-  // the graph's instances start unfinished
-  std::vector<uint8_t> z(kR, 0);
-  DAIC_HIP(hipMemcpy(b->a.done + (size_t)graph * kR, z.data(), kR, hipMemcpyHostToDevice));
-  return DAIC_OK;
+  DAIC_HIP(hipDeviceSynchronize());
+  hipStream_t s = b->stream;
+  float *v = b->a.v + off * kR, *dv = b->a.dv + off * kR, *c = b->a.c ? b->a.c + off * kR : nullptr;
+  // the unused right-hand sides are zero; the graph's instances start unfinished
+  hipLaunchKernelGGL(k_bclear, stage_grid(n * kR), dim3(256), 0, s, R < kR ? n * kR : 0, v, dv, c,
+                     b->a.done + (size_t)graph * kR);
+  auto put = [&](const double* from, float* to, float* rounding) {
+    return stage_move<false>(const_cast<double*>(from), n * R, 8, s, [&](const void* chunk, uint64_t first, uint64_t k) {
+      hipLaunchKernelGGL(k_bstage_in, stage_grid(k), dim3(256), 0, s, static_cast<const double*>(chunk), first, k, R, to,
+                         rounding);
+    });
+  };
+  const daic_status rc = put(v0, v, c);
+  return rc ? rc : put(dv1, dv, nullptr);
 }
 
 // Autotuner: times the claim kernel (sparse rounds and the claim that opens
@@ -2006,6 +2036,14 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
   return c.done ? DAIC_OK : DAIC_NOT_CONVERGED;
 }
 
+static daic_status batch_take(const daic_batch* b, const float* from, const float* c, uint64_t n, uint32_t R,
+                              double* host) {
+  hipStream_t s = b->stream;
+  return stage_move<true>(host, n * R, 8, s, [&](void* chunk, uint64_t first, uint64_t k) {
+    hipLaunchKernelGGL(k_bstage_out, stage_grid(k), dim3(256), 0, s, from, c, first, k, R, static_cast<double*>(chunk));
+  });
+}
+
 daic_status daic_batch_get(const daic_batch* b, uint32_t graph, double* v_out) {
   if (!b || !v_out) return fail(DAIC_E_INVALID, "null argument");
   if (graph >= b->G) return fail(DAIC_E_INVALID, "graph index out of range");
@@ -2013,14 +2051,8 @@ daic_status daic_batch_get(const daic_batch* b, uint32_t graph, double* v_out) {
   const uint32_t R = b->rhs[graph];
   if (n == 0) return DAIC_OK;
   DAIC_HIP(hipDeviceSynchronize());
-  std::vector<float> tv(n * kR), tc(n * kR, 0.0f);
-  DAIC_HIP(hipMemcpy(tv.data(), b->a.v + off * kR, n * kR * 4, hipMemcpyDeviceToHost));
-  if (b->a.c) DAIC_HIP(hipMemcpy(tc.data(), b->a.c + off * kR, n * kR * 4, hipMemcpyDeviceToHost));
-  for (uint64_t j = 0; j < n; ++j)
-    for (uint32_t r = 0; r < R; ++r) v_out[j * R + r] = (double)tv[j * kR + r] - (double)tc[j * kR + r];
-  return DAIC_OK;
+  return batch_take(b, b->a.v + off * kR, b->a.c ? b->a.c + off * kR : nullptr, n, R, v_out);
 }
-
 
 daic_status daic_batch_get_state(const daic_batch* b, uint32_t graph, double* v_out, double* dv_out,
                                  uint8_t* done_out) {
@@ -2034,10 +2066,8 @@ daic_status daic_batch_get_state(const daic_batch* b, uint32_t graph, double* v_
     if (rc) return rc;
   }
   if (dv_out && n) {
-    std::vector<float> td(n * kR);
-    DAIC_HIP(hipMemcpy(td.data(), b->a.dv + off * kR, n * kR * 4, hipMemcpyDeviceToHost));
-    for (uint64_t j = 0; j < n; ++j)
-      for (uint32_t r = 0; r < R; ++r) dv_out[j * R + r] = (double)td[j * kR + r];
+    daic_status rc = batch_take(b, b->a.dv + off * kR, nullptr, n, R, dv_out);
+    if (rc) return rc;
   }
   if (done_out) {
     uint8_t st[kR];

@@ -95,6 +95,15 @@ struct Partition {
   uint64_t per_block = 0;
 };
 
+// Held by every object with host transfers: the pinned buffers of the
+// transfers (daic_stage.h) are freed with the last one.
+struct StageUser {
+  StageUser();
+  ~StageUser();
+  StageUser(const StageUser&) = delete;
+  StageUser& operator=(const StageUser&) = delete;
+};
+
 // Learned scheduler hooks (defined with the scheduler network).
 daic_status learned_prepare(daic_problem* p, const daic_sched_model* model, hipStream_t s);
 // The multiplier array of learned rounds, and the enqueue of the scoring

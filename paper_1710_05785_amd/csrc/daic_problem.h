@@ -38,6 +38,7 @@ struct GraphCacheKey {
 };
 
 struct daic_problem {
+  daic::StageUser stage;
   const daic_graph* g = nullptr;
   daic_op op = DAIC_SUM;
   daic_g gk = DAIC_G_SRC_SCALE;

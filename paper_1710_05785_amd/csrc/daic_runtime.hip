@@ -17,6 +17,7 @@
 #include "daic_internal.h"
 #include "daic_kernels.h"
 #include "daic_problem.h"
+#include "daic_stage.h"
 
 namespace daic {
 
@@ -447,6 +448,20 @@ __global__ void k_fill(T* p, T val, uint64_t count) {
   uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   uint64_t st = (uint64_t)gridDim.x * blockDim.x;
   for (; i < count; i += st) p[i] = val;
+}
+
+// v and dv from the caller's device arrays, and a cleared compensation term,
+// in one launch (two copy calls and a fill took 270-440 us for 1-4 MB arrays,
+// most of it host time of the copies).
+template <typename T>
+__global__ void k_set_state(const T* v0, const T* dv1, uint64_t n, T* v, T* dv, float* c) {
+  uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  uint64_t st = (uint64_t)gridDim.x * blockDim.x;
+  for (; i < n; i += st) {
+    v[i] = v0[i];
+    dv[i] = dv1[i];
+    if (c) c[i] = 0.0f;
+  }
 }
 
 static uint32_t grid_for(uint64_t count, uint32_t block = 256) {
@@ -998,25 +1013,29 @@ daic_status daic_problem_set_init(daic_problem* p, const void* v0, const void* d
   if (!p || !v0 || !dv1) return fail(DAIC_E_INVALID, "null argument");
   const uint64_t n = p->g->dev.n;
   if (n == 0) return DAIC_OK;
-  if (p->st == ST_F64 || p->st == ST_U32 || p->st == ST_I32 || p->st == ST_F64MIN) {
-    size_t S = state_size(p->st);
-    DAIC_HIP(hipMemcpy(p->a.v, v0, n * S, hipMemcpyHostToDevice));
-    DAIC_HIP(hipMemcpy(p->a.dv, dv1, n * S, hipMemcpyHostToDevice));
-  } else {
-    const double* a = static_cast<const double*>(v0);
-    const double* b = static_cast<const double*>(dv1);
-    std::vector<float> tv(n), td(n), tc(n, 0.0f);
-    for (uint64_t j = 0; j < n; ++j) {
-      tv[j] = (float)a[j];
-      td[j] = (float)b[j];
-      // carry the FP32 rounding of v0 in the compensation term
-      tc[j] = (float)((double)tv[j] - a[j]);
-    }
-    DAIC_HIP(hipMemcpy(p->a.v, tv.data(), n * 4, hipMemcpyHostToDevice));
-    DAIC_HIP(hipMemcpy(p->a.dv, td.data(), n * 4, hipMemcpyHostToDevice));
-    if (p->a.c) DAIC_HIP(hipMemcpy(p->a.c, tc.data(), n * 4, hipMemcpyHostToDevice));
-  }
-  return DAIC_OK;
+  DAIC_HIP(hipDeviceSynchronize());
+  hipStream_t s = p->own_stream;
+  auto put = [&](const void* from, void* to, float* c) {
+    void* host = const_cast<void*>(from);
+    if (p->st == ST_F32 || p->st == ST_F32K)  // the compensation term carries the FP32 rounding of v0
+      return stage_move<false>(host, n, 8, s, [&](const void* chunk, uint64_t first, uint64_t k) {
+        hipLaunchKernelGGL((k_stage_in<double, float>), stage_grid(k), dim3(256), 0, s,
+                           static_cast<const double*>(chunk), first, k, static_cast<float*>(to), c);
+      });
+    if (state_size(p->st) == 8)
+      return stage_move<false>(host, n, 8, s, [&](const void* chunk, uint64_t first, uint64_t k) {
+        hipLaunchKernelGGL((k_stage_in<uint64_t, uint64_t>), stage_grid(k), dim3(256), 0, s,
+                           static_cast<const uint64_t*>(chunk), first, k, static_cast<uint64_t*>(to),
+                           static_cast<uint64_t*>(nullptr));
+      });
+    return stage_move<false>(host, n, 4, s, [&](const void* chunk, uint64_t first, uint64_t k) {
+      hipLaunchKernelGGL((k_stage_in<uint32_t, uint32_t>), stage_grid(k), dim3(256), 0, s,
+                         static_cast<const uint32_t*>(chunk), first, k, static_cast<uint32_t*>(to),
+                         static_cast<uint32_t*>(nullptr));
+    });
+  };
+  const daic_status rc = put(v0, p->a.v, p->a.c);
+  return rc ? rc : put(dv1, p->a.dv, nullptr);
 }
 
 static double per_edge_bytes(const daic_problem* p) {
@@ -1203,9 +1222,15 @@ daic_status daic_problem_set_init_device(daic_problem* p, const void* d_v0, cons
   if (n == 0) return DAIC_OK;
   hipStream_t s = hip_stream ? static_cast<hipStream_t>(hip_stream) : p->own_stream;
   const size_t S = state_size(p->st);
-  DAIC_HIP(hipMemcpyAsync(p->a.v, d_v0, n * S, hipMemcpyDeviceToDevice, s));
-  DAIC_HIP(hipMemcpyAsync(p->a.dv, d_dv1, n * S, hipMemcpyDeviceToDevice, s));
-  if (p->a.c) hipLaunchKernelGGL(k_fill<float>, dim3(grid_for(n)), dim3(256), 0, s, p->a.c, 0.0f, n);
+  if (S == 8)
+    hipLaunchKernelGGL(k_set_state<uint64_t>, dim3(grid_for(n)), dim3(256), 0, s, static_cast<const uint64_t*>(d_v0),
+                       static_cast<const uint64_t*>(d_dv1), n, static_cast<uint64_t*>(p->a.v),
+                       static_cast<uint64_t*>(p->a.dv), p->a.c);
+  else
+    hipLaunchKernelGGL(k_set_state<uint32_t>, dim3(grid_for(n)), dim3(256), 0, s, static_cast<const uint32_t*>(d_v0),
+                       static_cast<const uint32_t*>(d_dv1), n, static_cast<uint32_t*>(p->a.v),
+                       static_cast<uint32_t*>(p->a.dv), p->a.c);
+  DAIC_HIP(hipGetLastError());
   if (!hip_stream) DAIC_HIP(hipStreamSynchronize(s));
   return DAIC_OK;
 }
@@ -1503,23 +1528,27 @@ daic_status daic_problem_get(const daic_problem* p, void* v_out, void* dv_out) {
   const uint64_t n = p->g->dev.n;
   if (n == 0) return DAIC_OK;
   DAIC_HIP(hipDeviceSynchronize());
-  if (p->st == ST_F64 || p->st == ST_U32 || p->st == ST_I32 || p->st == ST_F64MIN) {
-    size_t S = state_size(p->st);
-    DAIC_HIP(hipMemcpy(v_out, p->a.v, n * S, hipMemcpyDeviceToHost));
-    if (dv_out) DAIC_HIP(hipMemcpy(dv_out, p->a.dv, n * S, hipMemcpyDeviceToHost));
-    return DAIC_OK;
-  }
-  std::vector<float> tv(n), tc(n, 0.0f);
-  DAIC_HIP(hipMemcpy(tv.data(), p->a.v, n * 4, hipMemcpyDeviceToHost));
-  if (p->a.c) DAIC_HIP(hipMemcpy(tc.data(), p->a.c, n * 4, hipMemcpyDeviceToHost));
-  double* vo = static_cast<double*>(v_out);
-  for (uint64_t j = 0; j < n; ++j) vo[j] = (double)tv[j] - (double)tc[j];
-  if (dv_out) {
-    DAIC_HIP(hipMemcpy(tv.data(), p->a.dv, n * 4, hipMemcpyDeviceToHost));
-    double* d = static_cast<double*>(dv_out);
-    for (uint64_t j = 0; j < n; ++j) d[j] = (double)tv[j];
-  }
-  return DAIC_OK;
+  hipStream_t s = p->own_stream;
+  auto take = [&](const void* from, const float* c, void* host) {
+    if (p->st == ST_F32 || p->st == ST_F32K)
+      return stage_move<true>(host, n, 8, s, [&](void* chunk, uint64_t first, uint64_t k) {
+        hipLaunchKernelGGL((k_stage_out<float, double>), stage_grid(k), dim3(256), 0, s,
+                           static_cast<const float*>(from), c, first, k, static_cast<double*>(chunk));
+      });
+    if (state_size(p->st) == 8)
+      return stage_move<true>(host, n, 8, s, [&](void* chunk, uint64_t first, uint64_t k) {
+        hipLaunchKernelGGL((k_stage_out<uint64_t, uint64_t>), stage_grid(k), dim3(256), 0, s,
+                           static_cast<const uint64_t*>(from), static_cast<const uint64_t*>(nullptr), first, k,
+                           static_cast<uint64_t*>(chunk));
+      });
+    return stage_move<true>(host, n, 4, s, [&](void* chunk, uint64_t first, uint64_t k) {
+      hipLaunchKernelGGL((k_stage_out<uint32_t, uint32_t>), stage_grid(k), dim3(256), 0, s,
+                         static_cast<const uint32_t*>(from), static_cast<const uint32_t*>(nullptr), first, k,
+                         static_cast<uint32_t*>(chunk));
+    });
+  };
+  const daic_status rc = take(p->a.v, p->a.c, v_out);
+  return rc || !dv_out ? rc : take(p->a.dv, nullptr, dv_out);
 }
 
 void daic_problem_destroy(daic_problem* p) {
