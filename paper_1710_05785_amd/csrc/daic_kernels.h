@@ -1,7 +1,7 @@
 // Device code of one DAIC round on gfx950 (64-lane wavefronts).
 //
 // A round (Eq. async of the paper applied to a selected set, Sec. 3.2/3.4):
-//   A2 k_sample_keys + k_sample, or k_radix_pass + k_radix_pick per digit
+//   A2 k_sample, or k_radix_pass + k_radix_pick per digit and k_ties
 //                           : threshold of the priority keys (sampled or exact)
 //   A3+A4 k_claim           : select, claim dv_j, fold v_j (+)= delta, compute
 //                             the message base mu_j, compact into degree bins
@@ -71,7 +71,6 @@ struct KArgs {
   uint64_t* blk_push_large;
   uint32_t* blk_ties;       // exact top-k: keys equal to tau per block
   uint32_t* rhist;          // exact top-k: radix histogram (kRadixCopies x kRadixBins counters)
-  uint64_t* skeys;          // sampled threshold: the round's sampled keys (kMaxSamples)
   uint64_t* off_ties;       // exclusive prefix of blk_ties
   double* part_r;           // residual partials per block
   uint64_t* part_n;         // pending-count partials per block
@@ -298,11 +297,8 @@ __device__ __forceinline__ void push_edge(const KArgs& a, uint64_t e, typename T
 // increment one counter at the same time; those atomics serialize.)
 // ---------------------------------------------------------------------------
 template <int ST>
-__global__ __launch_bounds__(256) void k_residual(KArgs a, int skip_dense = 0) {
+__device__ __forceinline__ void residual_block(const KArgs& a) {
   using S = typename Tr<ST>::S;
-  Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl)) return;
-  if (skip_dense && ctl->last_pull) return;  // a dense round's residual comes from k_pull_finish
   const uint32_t b = blockIdx.x;
   const uint64_t lo = (uint64_t)b * a.per_block;
   const uint64_t hi = min(a.n, lo + a.per_block);
@@ -348,6 +344,13 @@ __global__ __launch_bounds__(256) void k_residual(KArgs a, int skip_dense = 0) {
   }
 }
 
+template <int ST>
+__global__ __launch_bounds__(256) void k_residual(KArgs a, int skip_dense = 0) {
+  if (ctl_halted(a.ctl)) return;
+  if (skip_dense && a.ctl->last_pull) return;  // a dense round's residual comes from k_pull_finish
+  residual_block<ST>(a);
+}
+
 // The direction of the next round: a dense round (pull over in-edges) when
 // the next round is expected to do enough work. Sum problems: at least
 // pull_min vertices expected to update (min(pending, k_sel)). Min and max
@@ -366,28 +369,88 @@ __device__ __forceinline__ uint32_t next_is_dense(uint64_t nn, double pend_edges
   }
 }
 
-// Besides the residual, k_residual_final picks the direction of the next
-// round (next_is_dense). One block; it returns in the cases where k_residual
-// returned.
+// What a round's end sets besides the residual: the direction rule of the
+// next round, the start of an exact top-k selection (topk > 0: the number of
+// vertices it takes), and for learned runs the judge.
+struct RoundEnd {
+  uint64_t k_sel = 0, pull_min = 0;  // see next_is_dense
+  uint64_t topk = 0;
+  uint32_t learned = 0;
+};
+
+// Start of a round's radix select: nothing to do when all pending fit.
+__device__ __forceinline__ void topk_begin(Ctl* ctl, uint64_t pending, uint64_t k) {
+  const bool all = pending <= k;
+  ctl->sel_mode = all ? 0u : 2u;
+  ctl->radix_skip = all ? 1u : 0u;
+  ctl->k_rem = k;
+  ctl->radix_prefix = 0;
+}
+
+// Learned scheduling, before a round: remember the residual and decide
+// whether the round ranks by the network (exact top-k while exact rounds
+// are owed).
+__device__ __forceinline__ void learned_pre(Ctl* ctl) {
+  ctl->l_r0 = ctl->r;
+  ctl->l_rounds0 = ctl->rounds;
+  ctl->use_score = ctl->l_exact_left == 0 ? 1u : 0u;
+}
+
+// After the round: the judge's figure, the priority its updates realized
+// (sum over the selected vertices of |v (+) dv - v|) per message, as a
+// fraction of the residual at the round's start for sum problems (where the
+// residual is that same priority mass), in value units for min/max problems
+// (whose residual is a count). An exact round calibrates the judge; a
+// learned round below 0.8 x the last exact round's figure hands the next
+// kFallback rounds back to exact selection, and after kWindow learned rounds
+// one exact round recalibrates.
+template <bool SUM>
+__device__ __forceinline__ void learned_post(Ctl* ctl) {
+  constexpr uint32_t kFallback = 4, kWindow = 16;
+  const double r0 = ctl->l_r0;
+  double eff = ctl->l_gain / (double)(ctl->round_pushed > 1 ? ctl->round_pushed : 1);
+  if (SUM) eff /= r0 > 1e-300 ? r0 : 1e-300;
+  if (!ctl->use_score) {
+    ctl->l_exact_eff = eff;
+    ctl->l_exact_rounds += 1;
+    if (ctl->l_exact_left > 0) ctl->l_exact_left -= 1;
+    ctl->l_run = 0;
+  } else if (eff < 0.8 * ctl->l_exact_eff) {
+    ctl->l_exact_left = kFallback;
+    ctl->l_fallbacks += 1;
+  } else if (++ctl->l_run >= kWindow) {
+    ctl->l_exact_left = 1;
+  }
+}
+
+// One thread, after the residual, the counters and the stop flags of a
+// finished round (count_round 1) or of the run's starting state (0).
 template <int ST>
-__global__ __launch_bounds__(256) void k_residual_final(KArgs a, int count_round, uint64_t k_sel,
-                                                        uint64_t pull_min, int skip_dense = 0) {
+__device__ __forceinline__ void round_end(Ctl* ctl, int count_round, const RoundEnd& e) {
+  if (e.learned) {
+    if (count_round) learned_post<Tr<ST>::sum>(ctl);
+    if (!ctl_halted(ctl)) learned_pre(ctl);
+  }
+  if (e.topk && !ctl_halted(ctl)) topk_begin(ctl, ctl->pending, e.topk);
+}
+
+// The residual's totals (one block of 256).
+template <int ST>
+__device__ __forceinline__ void residual_totals(const KArgs& a, int count_round, const RoundEnd& e) {
   Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl)) return;
-  if (skip_dense && ctl->last_pull) return;
   double rr = 0.0;
   uint64_t nn = 0;
-  for (uint32_t i0 = threadIdx.x; i0 < a.blocks; i0 += 1024) {
-    double pr[4];
-    uint64_t pn[4];
+  for (uint32_t i0 = threadIdx.x; i0 < a.blocks; i0 += 2048) {
+    double pr[8];
+    uint64_t pn[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 8; ++u) {
       const uint32_t i = min(i0 + 256 * u, a.blocks - 1);
       pr[u] = a.part_r[i];
       pn[u] = a.part_n[i];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 8; ++u) {
       if (i0 + 256 * u >= a.blocks) break;
       rr += pr[u];
       nn += pn[u];
@@ -402,80 +465,178 @@ __global__ __launch_bounds__(256) void k_residual_final(KArgs a, int count_round
     bool done = Tr<ST>::sum ? (rr <= ctl->eps || nn == 0) : (nn == 0);
     ctl->done = done ? 1u : 0u;
     ctl->stop = (!done && ctl->rounds >= ctl->max_rounds) ? 1u : 0u;
-    ctl->pull = next_is_dense<ST>(nn, rr, k_sel, pull_min);  // rr: pending vertices' out-edges (min/max)
+    ctl->pull = next_is_dense<ST>(nn, rr, e.k_sel, e.pull_min);  // rr: pending vertices' out-edges (min/max)
+    round_end<ST>(ctl, count_round, e);
+  }
+}
+
+// Besides the residual, k_residual_final picks the direction of the next
+// round (next_is_dense). One block; it returns in the cases where k_residual
+// returned.
+template <int ST>
+__global__ __launch_bounds__(256) void k_residual_final(KArgs a, int count_round, RoundEnd e, int skip_dense = 0) {
+  if (ctl_halted(a.ctl)) return;
+  if (skip_dense && a.ctl->last_pull) return;
+  residual_totals<ST>(a, count_round, e);
+}
+
+// ---------------------------------------------------------------------------
+// Order statistics inside one workgroup of 1,024 threads.
+// ---------------------------------------------------------------------------
+// f(0), f(1), ..., f(N - 1) with constant arguments: the state's register
+// arrays are only ever indexed by constants (a loop with an exit would have
+// them moved as whole vectors).
+template <int N, int K = 0, typename F>
+__device__ __forceinline__ void unroll_each(const F& f) {
+  if constexpr (K < N) {
+    f(std::integral_constant<int, K>{});
+    unroll_each<N, K + 1>(f);
+  }
+}
+
+// z mod n (n < 2^32) by the reciprocal n_inv = floor((2^64 - 1) / n): the
+// quotient estimate is at most two below the true one.
+__device__ __forceinline__ uint32_t mod_by_inverse(uint64_t z, uint64_t n, uint64_t n_inv) {
+  uint64_t r = z - __umul64hi(z, n_inv) * n;
+  if (r >= n) r -= n;
+  if (r >= n) r -= n;
+  return (uint32_t)r;
+}
+
+constexpr uint32_t kKthList = 64;  // candidates ranked directly
+struct KthScratch {
+  uint32_t hist[2][256];
+  uint64_t list[kKthList];
+  uint32_t count;
+  uint32_t digit, cnt, above;  // a pass's result
+  uint64_t tau;
+  uint32_t equal, rem;
+};
+
+// The rank-th largest of the workgroup's keys (key(u) for u < NK, valid(u)
+// telling whether it counts; 1 <= rank <= valid keys), 8 bits per pass from
+// the top: *equal keys have that value and *rem of them are within the rank.
+// The digit most lanes of a wave share is added to the histogram once (the
+// leading digits of priorities agree, and LDS atomics of one address take
+// turns); one wave scans the histogram (sixteen doing so would take the issue
+// slots of the CU four times over); a digit holding few keys ends the passes,
+// its keys ranked against each other by one wave.
+template <typename Key, int NK, typename KeyF, typename ValidF>
+__device__ __forceinline__ Key block_kth(KthScratch& s, uint32_t rank, const KeyF& key, const ValidF& valid,
+                                         uint32_t* equal, uint32_t* rem) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  if (tid < 256) s.hist[0][tid] = 0;
+  if (tid == 0) s.count = 0;
+  __syncthreads();
+  Key prefix = 0, mask = 0;
+  uint32_t left = rank, buf = 0;
+  for (int shift = (int)sizeof(Key) * 8 - 8;; shift -= 8) {
+    uint32_t* h = s.hist[buf];
+    unroll_each<NK>([&](auto u) {
+      const Key k = key(u);
+      bool on = valid(u) && (k & mask) == prefix;
+      const uint32_t d = (uint32_t)(k >> shift) & 255u;
+      const uint64_t live = __ballot(on);
+      if (live) {
+        const uint32_t d0 = __builtin_amdgcn_readlane(d, (uint32_t)__ffsll((unsigned long long)live) - 1);
+        const uint64_t same = __ballot(on && d == d0);
+        on = on && d != d0;
+        if (on || lane == 0) atomicAdd(&h[on ? d : d0], on ? 1u : (uint32_t)__popcll(same));
+        if (lane == 0 && on) atomicAdd(&h[d0], (uint32_t)__popcll(same));
+      }
+    });
+    __syncthreads();
+    if (tid < 64) {
+      // bins from the top: lane l holds bins 255 - 4l - q
+      uint32_t c[4], sum = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        c[q] = h[255 - 4 * lane - q];
+        sum += c[q];
+      }
+      uint32_t above = wave_incl_scan(sum) - sum;
+      if (above < left && left <= above + sum) {  // one lane
+        uint32_t q = 0;
+        while (q < 3 && above + c[q] < left) above += c[q++];
+        s.digit = 255 - 4 * lane - q;
+        s.cnt = q == 0 ? c[0] : q == 1 ? c[1] : q == 2 ? c[2] : c[3];
+        s.above = above;
+      }
+    } else if (tid < 320) {
+      s.hist[buf ^ 1][tid - 64] = 0;
+    }
+    __syncthreads();
+    const uint32_t cnt = s.cnt;
+    left -= s.above;
+    prefix |= (Key)s.digit << shift;
+    mask |= (Key)255 << shift;
+    if (shift == 0) {
+      *equal = cnt;
+      *rem = left;
+      return prefix;
+    }
+    if (cnt <= kKthList) {
+      unroll_each<NK>([&](auto u) {
+        const Key k = key(u);
+        if (valid(u) && (k & mask) == prefix) s.list[atomicAdd(&s.count, 1u)] = (uint64_t)k;
+      });
+      __syncthreads();
+      if (tid < 64) {
+        const Key mine = (Key)s.list[min(lane, cnt - 1)];
+        uint32_t more = 0, same = 0;
+        for (uint32_t i = 0; i < cnt; ++i) {
+          const Key o = (Key)s.list[i];
+          more += o > mine ? 1u : 0u;
+          same += o == mine ? 1u : 0u;
+        }
+        if (lane < cnt && more < left && left <= more + same) {  // equal keys store the same values
+          s.tau = (uint64_t)mine;
+          s.equal = same;
+          s.rem = left - more;
+        }
+      }
+      __syncthreads();
+      *equal = s.equal;
+      *rem = s.rem;
+      return (Key)s.tau;
+    }
+    buf ^= 1;
   }
 }
 
 // ---------------------------------------------------------------------------
 // A2 (sampled): threshold = the rank-th largest of S sampled keys; a
-// threshold of 0 (no positive sample) selects every pending vertex.
-// k_sample_keys draws the S sampled keys (one thread each); k_sample then
-// ranks them: ceil(S / 64) workgroups, each loading all S keys into LDS,
-// whose four waves rank the same 64 samples against a quarter of the keys
-// each (keys above, keys equal). The rank-th largest is the sample with
-// above < rank <= above + equal; threads holding equal keys store the same
-// threshold.
+// threshold of 0 (no positive sample) selects every pending vertex. One
+// workgroup of 1,024 threads, up to four samples each: the draws and the
+// selection in one kernel take 9 us (S = 4,096), where a kernel that drew
+// them and one whose 64 workgroups ranked all pairs took 3 and 16-20 us.
 // ---------------------------------------------------------------------------
 template <int ST>
-__global__ __launch_bounds__(256) void k_sample_keys(KArgs a, uint32_t S_n, uint64_t seed, uint64_t round_override) {
-  if (a.score != nullptr && !a.ctl->use_score) a.score = nullptr;  // an exact round of a learned run
+__global__ __launch_bounds__(1024) void k_sample(KArgs a, uint32_t S_n, uint32_t rank, uint64_t seed, uint64_t n_inv,
+                                                 uint64_t round_override) {
   using S = typename Tr<ST>::S;
-  Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl)) return;
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= S_n) return;
-  const uint64_t round = round_override != ~0ull ? round_override : ctl->rounds;
-  const uint64_t j = splitmix64_at(seed, round * (uint64_t)S_n + i) % a.n;
-  const float sc = a.score != nullptr ? a.score[j] : 1.f;
-  a.skeys[i] = (uint64_t)sel_key_loaded<ST>(a, static_cast<const S*>(a.v)[j], static_cast<const S*>(a.dv)[j], sc);
-}
-
-template <int ST>
-__global__ __launch_bounds__(256) void k_sample(KArgs a, uint32_t S_n, uint32_t rank) {
   using Key = typename Tr<ST>::Key;
   Ctl* ctl = a.ctl;
   if (ctl_halted(ctl)) return;
-  __shared__ Key keys[kMaxSamples];
-  __shared__ uint32_t s_above[4][64], s_equal[4][64];
+  __shared__ KthScratch scratch;
   const uint32_t tid = threadIdx.x;
-  constexpr uint32_t PER = kMaxSamples / 256;
-  Key kk[PER];
+  const uint64_t round = round_override != ~0ull ? round_override : ctl->rounds;
+  S v[4], dv[4];
 #pragma unroll
-  for (uint32_t q = 0; q < PER; ++q) kk[q] = (Key)a.skeys[min(tid + 256 * q, S_n - 1)];
-#pragma unroll
-  for (uint32_t q = 0; q < PER; ++q)
-    if (tid + 256 * q < S_n) keys[tid + 256 * q] = kk[q];
-  __syncthreads();
-  const uint32_t lane = tid & 63, wave = tid >> 6;
-  const uint32_t mine_i = min(blockIdx.x * 64 + lane, S_n - 1);
-  const Key mine = keys[mine_i];
-  // this wave's quarter of the keys; every lane reads the same key (broadcast)
-  const uint32_t quarter = (S_n + 3) / 4;
-  const uint32_t i0 = min(S_n, wave * quarter), i1 = min(S_n, i0 + quarter);
-  uint32_t above = 0, equal = 0, i = i0;
-  for (; i + 8 <= i1; i += 8) {
-    Key k[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) k[u] = keys[i + u];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      above += k[u] > mine ? 1u : 0u;
-      equal += k[u] == mine ? 1u : 0u;
-    }
+  for (uint32_t u = 0; u < 4; ++u) {
+    const uint64_t j = mod_by_inverse(splitmix64_at(seed, round * (uint64_t)S_n + tid + u * 1024), a.n, n_inv);
+    v[u] = static_cast<const S*>(a.v)[j];
+    dv[u] = static_cast<const S*>(a.dv)[j];
   }
-  for (; i < i1; ++i) {
-    above += keys[i] > mine ? 1u : 0u;
-    equal += keys[i] == mine ? 1u : 0u;
-  }
-  s_above[wave][lane] = above;
-  s_equal[wave][lane] = equal;
-  __syncthreads();
-  if (wave != 0 || blockIdx.x * 64 + lane >= S_n) return;
-  above = s_above[0][lane] + s_above[1][lane] + s_above[2][lane] + s_above[3][lane];
-  equal = s_equal[0][lane] + s_equal[1][lane] + s_equal[2][lane] + s_equal[3][lane];
-  if (above < rank && rank <= above + equal) {  // every such thread stores the same values
-    __hip_atomic_store(&ctl->sel_mode, mine == 0 ? 0u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&ctl->tau, (uint64_t)mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  Key key[4];
+#pragma unroll
+  for (uint32_t u = 0; u < 4; ++u) key[u] = prio_key<ST>(v[u], dv[u]);
+  uint32_t equal, rem;
+  const Key tau = block_kth<Key, 4>(
+      scratch, rank, [&](auto u) { return key[u]; }, [&](auto u) { return tid + u * 1024 < S_n; }, &equal, &rem);
+  if (tid == 0) {
+    ctl->sel_mode = tau == 0 ? 0u : 1u;
+    ctl->tau = (uint64_t)tau;
   }
 }
 
@@ -508,46 +669,6 @@ static __global__ void k_init_ctl(Ctl* ctl, double eps, uint64_t max_rounds) {
   ctl->l_exact_eff = 0.0;
   ctl->l_fallbacks = 0;
   ctl->l_exact_rounds = 0;
-}
-
-// Learned scheduling, before a round: remember the residual and decide
-// whether the round ranks by the network (exact top-k while exact rounds
-// are owed).
-static __global__ void k_learned_pre(Ctl* ctl) {
-  if (ctl_halted(ctl)) return;
-  ctl->l_r0 = ctl->r;
-  ctl->l_rounds0 = ctl->rounds;
-  ctl->use_score = ctl->l_exact_left == 0 ? 1u : 0u;
-}
-
-// After the round: the judge's figure, the priority its updates realized
-// (sum over the selected vertices of |v (+) dv - v|) per message, as a
-// fraction of the residual at the round's start for sum problems (where the
-// residual is that same priority mass), in value units for min/max problems
-// (whose residual is a count). An exact round calibrates the judge; a
-// learned round below 0.8 x the last exact round's figure hands the next
-// kFallback rounds back to exact selection, and after kWindow learned rounds
-// one exact round recalibrates.
-template <bool SUM>
-__global__ void k_learned_post(Ctl* ctl) {
-  constexpr uint32_t kFallback = 4, kWindow = 16;
-  if (ctl->rounds == ctl->l_rounds0) return;  // no round was run
-  ctl->l_rounds0 = ctl->rounds;
-  const double r0 = ctl->l_r0;
-  double eff = ctl->l_gain / (double)(ctl->round_pushed > 1 ? ctl->round_pushed : 1);
-  if (SUM) eff /= r0 > 1e-300 ? r0 : 1e-300;
-  if (!ctl->use_score) {
-    ctl->l_exact_eff = eff;
-    ctl->l_exact_rounds += 1;
-    if (ctl->l_exact_left > 0) ctl->l_exact_left -= 1;
-    ctl->l_run = 0;
-  } else if (eff < 0.8 * ctl->l_exact_eff) {
-    ctl->l_exact_left = kFallback;
-    ctl->l_fallbacks += 1;
-  } else if (++ctl->l_run >= kWindow) {
-    ctl->l_exact_left = 1;
-  }
-  ctl->use_score = 1;
 }
 
 // The stop flags are recomputed by the next residual.
@@ -594,19 +715,13 @@ __device__ __forceinline__ void radix_digit(int key_bits, int pass, int& shift, 
   width = top - shift;
 }
 
-// One block of 256 threads: clears the histograms and starts the select.
+// One block of 256 threads: clears the histograms and starts the select (the
+// rounds of a run start it when the round before ends, and every pick leaves
+// the histograms clear).
 static __global__ __launch_bounds__(256) void k_topk_init(Ctl* ctl, uint32_t* rhist, uint64_t k) {
   for (uint32_t i = threadIdx.x; i < kRadixBins * kRadixCopies; i += 256) rhist[i] = 0;
   if (threadIdx.x != 0 || ctl_halted(ctl)) return;
-  if (ctl->pending <= k) {
-    ctl->sel_mode = 0;
-    ctl->radix_skip = 1;
-  } else {
-    ctl->sel_mode = 2;
-    ctl->radix_skip = 0;
-    ctl->k_rem = k;
-    ctl->radix_prefix = 0;
-  }
+  topk_begin(ctl, ctl->pending, k);
 }
 
 // One pass: every workgroup counts the digits of the keys that match the
@@ -660,12 +775,13 @@ __global__ __launch_bounds__(256) void k_radix_pass(KArgs a, int pass) {
   }
 }
 
-// After a pass (one block of 256 threads): the digit that holds the
+// After a pass (one block of 1,024 threads): the digit that holds the
 // k_rem-th largest key, from the sum of the histogram copies (bins scanned
-// from the top, 8 per thread); it is fixed in the prefix and the copies are
-// cleared for the next pass.
+// from the top, two per thread, so that every load is in flight at once: a
+// block of 256 with eight bins each took 9 us); it is fixed in the prefix and
+// the copies are cleared for the next pass.
 template <int ST>
-__global__ __launch_bounds__(256) void k_radix_pick(KArgs a, int pass) {
+__global__ __launch_bounds__(1024) void k_radix_pick(KArgs a, int pass) {
   using Key = typename Tr<ST>::Key;
   Ctl* ctl = a.ctl;
   if (ctl_halted(ctl) || ctl->radix_skip) return;
@@ -673,38 +789,35 @@ __global__ __launch_bounds__(256) void k_radix_pick(KArgs a, int pass) {
   int shift, width;
   radix_digit(kBits, pass, shift, width);
   const uint32_t nbins = 1u << width;
-  const uint32_t tid = threadIdx.x;
-  __shared__ uint32_t s_found;
-  // bins from the top: thread t holds bins nbins-1-8t-q, q = 0..7
-  uint32_t c[8];
-  uint32_t sum[1] = {0};
+  const uint32_t tid = threadIdx.x, wave = tid >> 6;
+  __shared__ uint32_t s_found, s_wave[16];
+  // bins from the top: thread t holds bins nbins - 1 - 2t - q, q = 0, 1
+  uint32_t x[2][kRadixCopies];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const uint32_t r = tid * 8 + q;
-    uint32_t x[kRadixCopies];
+  for (int q = 0; q < 2; ++q) {
+    const uint32_t r = tid * 2 + q;
 #pragma unroll
     for (uint32_t cp = 0; cp < kRadixCopies; ++cp)
-      x[cp] = r < nbins ? a.rhist[cp * kRadixBins + nbins - 1 - r] : 0u;
-    c[q] = 0;
-#pragma unroll
-    for (uint32_t cp = 0; cp < kRadixCopies; ++cp) c[q] += x[cp];
-    sum[0] += c[q];
+      x[q][cp] = r < nbins ? a.rhist[cp * kRadixBins + nbins - 1 - r] : 0u;
   }
-  uint32_t tot[1];
-  const uint32_t mine = sum[0];
-  block_excl_scan<1>(sum, tot);  // sum[0] = keys in the bins above this thread's
+  uint32_t c[2] = {0, 0};
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (uint32_t cp = 0; cp < kRadixCopies; ++cp) c[q] += x[q][cp];
+  const uint32_t mine = c[0] + c[1];
+  const uint32_t incl = wave_incl_scan(mine);
+  if (lane_id() == 63) s_wave[wave] = incl;
   if (tid == 0) s_found = 0;
   __syncthreads();
+  uint64_t above = incl - mine;  // keys in the bins above this thread's
+#pragma unroll
+  for (uint32_t w = 0; w < 16; ++w) above += w < wave ? s_wave[w] : 0u;
   const uint64_t k = ctl->k_rem;
-  if ((uint64_t)sum[0] < k && k <= (uint64_t)sum[0] + mine) {
-    uint64_t cum = sum[0];
-    int q = 0;
-    for (; q < 7; ++q) {
-      if (cum + c[q] >= k) break;
-      cum += c[q];
-    }
-    const uint64_t d = nbins - 1 - (tid * 8 + q);
-    const uint64_t rem = k - cum;
+  if (above < k && k <= above + mine) {  // one thread
+    const int q = above + c[0] >= k ? 0 : 1;
+    const uint64_t d = nbins - 1 - (tid * 2 + q);
+    const uint64_t rem = k - above - (q ? c[0] : 0u);
     ctl->k_rem = rem;
     ctl->radix_prefix |= d << shift;
     if (shift == 0) {
@@ -719,13 +832,17 @@ __global__ __launch_bounds__(256) void k_radix_pick(KArgs a, int pass) {
     ctl->sel_mode = 0;
     ctl->radix_skip = 1;
   }
-  for (uint32_t i = tid; i < nbins; i += 256)
 #pragma unroll
-    for (uint32_t cp = 0; cp < kRadixCopies; ++cp) a.rhist[cp * kRadixBins + i] = 0;
+  for (int q = 0; q < 2; ++q)
+    if (tid * 2 + q < nbins)
+#pragma unroll
+      for (uint32_t cp = 0; cp < kRadixCopies; ++cp) a.rhist[cp * kRadixBins + tid * 2 + q] = 0;
 }
 
+// Keys equal to the threshold, where only some of them are taken: the count
+// of every block and, by the block that ends last, their exclusive prefix.
 template <int ST>
-__global__ __launch_bounds__(256) void k_tie_count(KArgs a) {
+__global__ __launch_bounds__(256) void k_ties(KArgs a) {
   if (a.score != nullptr && !a.ctl->use_score) a.score = nullptr;  // an exact round of a learned run
   using S = typename Tr<ST>::S;
   using Key = typename Tr<ST>::Key;
@@ -753,7 +870,35 @@ __global__ __launch_bounds__(256) void k_tie_count(KArgs a) {
       cnt += (j0 + 256 * u < hi && sel_key_loaded<ST>(a, vv[u], dd[u], sc[u]) == tau) ? 1u : 0u;
   }
   cnt = block_sum256(cnt);
-  if (threadIdx.x == 0) a.blk_ties[blockIdx.x] = cnt;
+  __shared__ uint32_t s_last, s_wave[4];
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&a.blk_ties[blockIdx.x], cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence();
+    s_last = atomicAdd(&ctl->ticket, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  constexpr uint32_t PER = kMaxScanBlocks / 256;  // blocks per thread, consecutive
+  uint32_t x[PER], sum = 0;
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint32_t i = threadIdx.x * PER + u;
+    x[u] = i < gridDim.x ? __hip_atomic_load(&a.blk_ties[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    sum += x[u];
+  }
+  const uint32_t incl = wave_incl_scan(sum), wave = threadIdx.x >> 6;
+  if (lane_id() == 63) s_wave[wave] = incl;
+  __syncthreads();
+  uint64_t at = incl - sum;
+  for (uint32_t w = 0; w < wave; ++w) at += s_wave[w];
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint32_t i = threadIdx.x * PER + u;
+    if (i < gridDim.x) a.off_ties[i] = at;
+    at += x[u];
+  }
+  if (threadIdx.x == 0) ctl->ticket = 0;
 }
 
 // Progress metric sum_j v_j of the current state (FP64; min problems skip
@@ -776,44 +921,6 @@ __global__ __launch_bounds__(256) void k_progress(KArgs a, double* out) {
   }
   s = block_sum256(s);
   if (threadIdx.x == 0) atomicAdd(out, s);
-}
-
-// Exclusive prefix of per-block counts (one block of 1024 threads).
-__device__ __forceinline__ void excl_prefix_1024(const uint32_t* in, uint64_t* out, uint32_t nb,
-                                                 uint64_t* total) {
-  __shared__ uint64_t s_w[16];
-  __shared__ uint64_t s_carry;
-  if (threadIdx.x == 0) s_carry = 0;
-  __syncthreads();
-  for (uint32_t base = 0; base < nb; base += 1024) {
-    uint32_t i = base + threadIdx.x;
-    uint64_t x = i < nb ? in[i] : 0;
-    // wave inclusive scan in 64 bits
-    uint64_t s = x;
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      uint64_t y = __shfl_up(s, d, 64);
-      if (lane >= (uint32_t)d) s += y;
-    }
-    if (lane == 63) s_w[threadIdx.x >> 6] = s;
-    __syncthreads();
-    uint64_t off = s_carry;
-    for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) off += s_w[w];
-    if (i < nb) out[i] = off + s - x;
-    __syncthreads();
-    if (threadIdx.x == 1023) s_carry = off + s;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    out[nb] = s_carry;
-    if (total) *total = s_carry;
-  }
-}
-
-static __global__ __launch_bounds__(1024) void k_tie_scan(KArgs a) {
-  if (ctl_halted(a.ctl) || a.ctl->sel_mode != 2) return;
-  excl_prefix_1024(a.blk_ties, a.off_ties, a.blocks, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1371,7 +1478,7 @@ __global__ __launch_bounds__(256) void k_pull_stream(KArgs a) {
 // pull's partials and the cut targets' final dv; the last block to finish
 // adds the per-block partials in a fixed order.
 template <int ST>
-__global__ __launch_bounds__(256) void k_pull_finish(KArgs a, uint32_t nf, uint64_t k_sel, uint64_t pull_min) {
+__global__ __launch_bounds__(256) void k_pull_finish(KArgs a, uint32_t nf, RoundEnd e) {
   using S = typename Tr<ST>::S;
   if constexpr (Tr<ST>::sum) {
     Ctl* ctl = a.ctl;
@@ -1416,8 +1523,9 @@ __global__ __launch_bounds__(256) void k_pull_finish(KArgs a, uint32_t nf, uint6
       const bool done = rr <= ctl->eps || nn == 0;
       ctl->done = done ? 1u : 0u;
       ctl->stop = (!done && ctl->rounds >= ctl->max_rounds) ? 1u : 0u;
-      ctl->pull = (k_sel != 0 && (nn < k_sel ? nn : k_sel) >= pull_min) ? 1u : 0u;
+      ctl->pull = next_is_dense<ST>(nn, rr, e.k_sel, e.pull_min);
       ctl->ticket = 0;
+      round_end<ST>(ctl, 1, e);
     }
   }
 }

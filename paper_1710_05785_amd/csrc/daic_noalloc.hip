@@ -24,8 +24,7 @@ constexpr size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign;
 // kMaxScanBlocks blocks whatever n is, so the size does not depend on n.
 constexpr size_t kOffCtl = 0;
 constexpr size_t kOffHist = align_up(kOffCtl + sizeof(Ctl));
-constexpr size_t kOffKeys = align_up(kOffHist + (size_t)kRadixBins * kRadixCopies * 4);
-constexpr size_t kOffTies = align_up(kOffKeys + (size_t)kMaxSamples * 8);
+constexpr size_t kOffTies = align_up(kOffHist + (size_t)kRadixBins * kRadixCopies * 4);
 constexpr size_t kOffTieOff = align_up(kOffTies + (size_t)kMaxScanBlocks * 4);
 constexpr size_t kOffPartR = align_up(kOffTieOff + ((size_t)kMaxScanBlocks + 1) * 8);
 constexpr size_t kOffPartN = align_up(kOffPartR + (size_t)kMaxScanBlocks * 8);
@@ -79,7 +78,7 @@ void enqueue_select(const KArgs& a, const daic_run_opts* o, uint64_t round, doub
   const uint64_t n = a.n;
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(1), 0, s, a.ctl, 0.0, ~0ull);
   hipLaunchKernelGGL(k_residual<ST>, dim3(a.blocks), dim3(256), 0, s, a, 0);
-  hipLaunchKernelGGL(k_residual_final<ST>, dim3(1), dim3(256), 0, s, a, 0, 0ull, 0ull, 0);
+  hipLaunchKernelGGL(k_residual_final<ST>, dim3(1), dim3(256), 0, s, a, 0, RoundEnd{}, 0);
   hipLaunchKernelGGL(k_clear_done, dim3(1), dim3(1), 0, s, a.ctl);  // the selection runs on a finished state too
   if (o->sched == DAIC_SCHED_ALL) {
     hipLaunchKernelGGL(k_select_all, dim3(1), dim3(1), 0, s, a.ctl);
@@ -88,8 +87,7 @@ void enqueue_select(const KArgs& a, const daic_run_opts* o, uint64_t round, doub
   } else if (o->sched == DAIC_SCHED_TOPK_SAMPLED) {
     const uint32_t S = o->n_samples ? o->n_samples : kMaxSamples;
     const uint32_t rank = (uint32_t)std::max(1.0, std::ceil(o->priority_fraction * (double)S));
-    hipLaunchKernelGGL(k_sample_keys<ST>, dim3((S + 255) / 256), dim3(256), 0, s, a, S, o->seed, round);
-    hipLaunchKernelGGL(k_sample<ST>, dim3((S + 63) / 64), dim3(256), 0, s, a, S, rank);
+    hipLaunchKernelGGL(k_sample<ST>, dim3(1), dim3(1024), 0, s, a, S, rank, o->seed, ~0ull / n, round);
   } else {
     uint64_t k = (uint64_t)std::ceil(o->priority_fraction * (double)n);
     if (k < 1) k = 1;
@@ -97,10 +95,9 @@ void enqueue_select(const KArgs& a, const daic_run_opts* o, uint64_t round, doub
     hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(256), 0, s, a.ctl, a.rhist, k);
     for (int pass = 0; pass < radix_passes<Key>(); ++pass) {
       hipLaunchKernelGGL(k_radix_pass<ST>, dim3(hgrid), dim3(256), 0, s, a, pass);
-      hipLaunchKernelGGL(k_radix_pick<ST>, dim3(1), dim3(256), 0, s, a, pass);
+      hipLaunchKernelGGL(k_radix_pick<ST>, dim3(1), dim3(1024), 0, s, a, pass);
     }
-    hipLaunchKernelGGL(k_tie_count<ST>, dim3(a.blocks), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_tie_scan, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(k_ties<ST>, dim3(a.blocks), dim3(256), 0, s, a);
   }
   // row offsets are not read by the selection-only claim
   hipLaunchKernelGGL((k_claim<ST, G, uint32_t, true>), dim3(a.blocks), dim3(256), 0, s, a);
@@ -143,7 +140,6 @@ daic_status daic_select_frontier_noalloc(daic_op op, daic_dtype state, uint64_t 
   KArgs a{};
   a.ctl = reinterpret_cast<Ctl*>(base + kOffCtl);
   a.rhist = reinterpret_cast<uint32_t*>(base + kOffHist);
-  a.skeys = reinterpret_cast<uint64_t*>(base + kOffKeys);
   a.blk_ties = reinterpret_cast<uint32_t*>(base + kOffTies);
   a.off_ties = reinterpret_cast<uint64_t*>(base + kOffTieOff);
   a.part_r = reinterpret_cast<double*>(base + kOffPartR);

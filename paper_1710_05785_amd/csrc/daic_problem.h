@@ -29,10 +29,11 @@ struct GraphCacheKey {
   const float* score = nullptr;
   const void* model = nullptr;   // learned rounds: the network and its version (weights,
   uint64_t model_version = 0;    // feature scales and BF16 copies captured by the graph)
-  uint64_t k_sel = 0, pull_min = 0;
+  daic::RoundEnd end;
   bool operator==(const GraphCacheKey& o) const {
     return sched == o.sched && k == o.k && S == o.S && q == o.q && seed == o.seed && K == o.K &&
-           stream == o.stream && score == o.score && k_sel == o.k_sel && pull_min == o.pull_min &&
+           stream == o.stream && score == o.score && end.k_sel == o.end.k_sel &&
+           end.pull_min == o.end.pull_min && end.topk == o.end.topk && end.learned == o.end.learned &&
            model == o.model && model_version == o.model_version;
   }
 };
@@ -84,8 +85,7 @@ struct daic_problem {
   void* tile_wr = nullptr;       // weights in their tile order (EDGE_SCALE)
   uint32_t tile_grid = 2048;     // workgroups of k_tile_pull (at most)
   uint32_t tfin_grid = 4096;     // workgroups of k_tile_finish (at most)
-  uint64_t k_sel = 0;      // dense-round rule of the current run (see k_residual)
-  uint64_t pull_min = 0;
+  daic::RoundEnd end;      // what the end of a round sets in the current run
   // learned scheduler state (allocated on first use)
   bool learned_ready = false;
   uint32_t* last_upd = nullptr;  // 1 + round of the last update of each vertex, 0 = never updated
@@ -150,6 +150,8 @@ bool get_ops(const daic_problem* p, Ops* out);
 daic_status check_opts(const daic_problem* p, const daic_run_opts* o);
 daic_status dense_rounds_setup(daic_problem* p, const daic_run_opts* o, hipStream_t s);
 void apply_run_opts(daic_problem* p, const daic_run_opts* o);
+// Clears the radix histograms at the start of a run of exact selections.
+void clear_radix(daic_problem* p, hipStream_t s);
 // Fourth condition of Sec. 3.1 on the current state (needs the constant c).
 daic_status check_init(daic_problem* p, double tol, uint64_t* mismatches, hipStream_t s);
 // Runs of small problems: whether a run takes the one-workgroup form, and the

@@ -172,12 +172,12 @@ struct Impl {
 
   static void residual(daic_problem* p, hipStream_t s, int count_round) {
     hipLaunchKernelGGL(k_residual<ST>, dim3(p->a.blocks), dim3(256), 0, s, p->a, 0);
-    hipLaunchKernelGGL(k_residual_final<ST>, dim3(1), dim3(256), 0, s, p->a, count_round, p->k_sel, p->pull_min, 0);
+    hipLaunchKernelGGL(k_residual_final<ST>, dim3(1), dim3(256), 0, s, p->a, count_round, p->end, 0);
   }
 
   // Threshold of a round (A2) for the given rule.
   static void threshold(daic_problem* p, const daic_run_opts* o, hipStream_t s, const KArgs& a,
-                        uint64_t round_override, Prof* pr) {
+                        uint64_t round_override, Prof* pr, bool begin = false) {
     const uint64_t n = p->a.n;
     if (o->sched == DAIC_SCHED_ALL) {
       launch(pr, "select_all", s, [&] { hipLaunchKernelGGL(k_select_all, dim3(1), dim3(1), 0, s, a.ctl); });
@@ -188,8 +188,7 @@ struct Impl {
       uint32_t S = o->n_samples ? o->n_samples : kMaxSamples;
       uint32_t rank = (uint32_t)std::max(1.0, std::ceil(o->priority_fraction * (double)S));
       launch(pr, "sample_threshold", s, [&] {
-        hipLaunchKernelGGL(k_sample_keys<ST>, dim3((S + 255) / 256), dim3(256), 0, s, a, S, o->seed, round_override);
-        hipLaunchKernelGGL(k_sample<ST>, dim3((S + 63) / 64), dim3(256), 0, s, a, S, rank);
+        hipLaunchKernelGGL(k_sample<ST>, dim3(1), dim3(1024), 0, s, a, S, rank, o->seed, ~0ull / n, round_override);
       });
     } else {  // exact top-k (also the learned rule, on the learned keys)
       uint64_t k = (uint64_t)std::ceil(o->priority_fraction * (double)n);
@@ -197,13 +196,13 @@ struct Impl {
       const int passes = radix_passes<Key>();
       uint32_t hgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(1024, (n + 1023) / 1024));
       launch(pr, "topk_radix", s, [&] {
-        hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(256), 0, s, a.ctl, a.rhist, k);
+        // a run's selections are started by the end of the round before (RoundEnd)
+        if (begin) hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(256), 0, s, a.ctl, a.rhist, k);
         for (int pass = 0; pass < passes; ++pass) {
           hipLaunchKernelGGL(k_radix_pass<ST>, dim3(hgrid), dim3(256), 0, s, a, pass);
-          hipLaunchKernelGGL(k_radix_pick<ST>, dim3(1), dim3(256), 0, s, a, pass);
+          hipLaunchKernelGGL(k_radix_pick<ST>, dim3(1), dim3(1024), 0, s, a, pass);
         }
-        hipLaunchKernelGGL(k_tie_count<ST>, dim3(a.blocks), dim3(256), 0, s, a);
-        hipLaunchKernelGGL(k_tie_scan, dim3(1), dim3(1024), 0, s, a);
+        hipLaunchKernelGGL(k_ties<ST>, dim3(a.blocks), dim3(256), 0, s, a);
       });
     }
   }
@@ -221,51 +220,45 @@ struct Impl {
     launch(pr, "push_edges", s, [&] {
       hipLaunchKernelGGL((k_push<ST, G, RowT>), dim3(2 * push_grid()), dim3(64), 0, s, a, push_grid());
     });
-    if (p->pull_ready && p->tile_ready && !Tr<ST>::sum) {  // dense rounds of min and max problems
+    if (p->pull_ready && p->tile_ready) {  // dense rounds through the tiled in-edges
       const TileArgs t = tile_args(p);
       const uint32_t np = tile_pull_grid(p), nfin = tile_finish_grid(p);
       launch(pr, "pull_tile", s, [&] {
-        if (t.tw > kNarrowTW) hipLaunchKernelGGL((k_tile_pull_mm<ST, G, 1024>), dim3(np), dim3(1024), 0, s, a, t);
-        else hipLaunchKernelGGL((k_tile_pull_mm<ST, G, 256>), dim3(np), dim3(256), 0, s, a, t);
+        if constexpr (Tr<ST>::sum) {
+          if (t.tw > kNarrowTW) hipLaunchKernelGGL((k_tile_pull<ST, G, false, 1024>), dim3(np), dim3(1024), 0, s, a, t);
+          else hipLaunchKernelGGL((k_tile_pull<ST, G, false, 256>), dim3(np), dim3(256), 0, s, a, t);
+        } else {
+          if (t.tw > kNarrowTW) hipLaunchKernelGGL((k_tile_pull_mm<ST, G, 1024>), dim3(np), dim3(1024), 0, s, a, t);
+          else hipLaunchKernelGGL((k_tile_pull_mm<ST, G, 256>), dim3(np), dim3(256), 0, s, a, t);
+        }
       });
-      launch(pr, "pull_tile_finish", s, [&] {
-        hipLaunchKernelGGL((k_tile_finish_mm<ST, G>), dim3(nfin), dim3(256), 0, s, a, t);
+      launch(pr, "settle", s, [&] {
+        hipLaunchKernelGGL((k_settle<ST, G>), dim3(std::max(nfin, a.blocks)), dim3(256), 0, s, a, t, nfin);
       });
-      launch(pr, "pull_tile_total", s, [&] {
-        hipLaunchKernelGGL((k_tile_total<ST, false>), dim3(1), dim3(256), 0, s, a, t, np, nfin, p->k_sel, p->pull_min);
+      launch(pr, "total", s, [&] {
+        hipLaunchKernelGGL(k_total<ST>, dim3(1), dim3(256), 0, s, a, t, np, nfin, p->end);
       });
-    } else if (p->pull_ready && p->tile_ready) {  // dense rounds through the tiled in-edges
-      const TileArgs t = tile_args(p);
-      const uint32_t np = tile_pull_grid(p), nfin = tile_finish_grid(p);
-      launch(pr, "pull_tile", s, [&] {
-        if (t.tw > kNarrowTW) hipLaunchKernelGGL((k_tile_pull<ST, G, false, 1024>), dim3(np), dim3(1024), 0, s, a, t);
-        else hipLaunchKernelGGL((k_tile_pull<ST, G, false, 256>), dim3(np), dim3(256), 0, s, a, t);
-      });
-      launch(pr, "pull_tile_finish", s, [&] {
-        hipLaunchKernelGGL((k_tile_finish<ST, G, false>), dim3(nfin), dim3(256), 0, s, a, t);
-      });
-      launch(pr, "pull_tile_total", s, [&] {
-        hipLaunchKernelGGL((k_tile_total<ST, false>), dim3(1), dim3(256), 0, s, a, t, np, nfin, p->k_sel, p->pull_min);
-      });
-    } else if (p->pull_ready) {
+      return;
+    }
+    if (p->pull_ready) {
       const uint32_t nf = fused_grid(p);
       launch(pr, "pull_stream", s, [&] {
         hipLaunchKernelGGL((k_pull_stream<ST, G>), dim3(nf), dim3(256), 0, s, a);
       });
       launch(pr, "pull_finish", s, [&] {
-        hipLaunchKernelGGL(k_pull_finish<ST>, dim3(finish_grid(p)), dim3(256), 0, s, a, nf, p->k_sel, p->pull_min);
+        hipLaunchKernelGGL(k_pull_finish<ST>, dim3(finish_grid(p)), dim3(256), 0, s, a, nf, p->end);
       });
     }
     launch(pr, "residual", s, [&] {
       const int skip = p->pull_ready ? 1 : 0;
       hipLaunchKernelGGL(k_residual<ST>, dim3(a.blocks), dim3(256), 0, s, a, skip);
-      hipLaunchKernelGGL(k_residual_final<ST>, dim3(1), dim3(256), 0, s, a, 1, p->k_sel, p->pull_min, skip);
+      hipLaunchKernelGGL(k_residual_final<ST>, dim3(1), dim3(256), 0, s, a, 1, p->end, skip);
     });
   }
 
   static void select(daic_problem* p, const daic_run_opts* o, hipStream_t s, uint64_t round_override) {
     KArgs a = p->a;
-    threshold(p, o, s, a, round_override, nullptr);
+    threshold(p, o, s, a, round_override, nullptr, true);
     hipLaunchKernelGGL((k_claim<ST, G, RowT, true>), dim3(a.blocks), dim3(256), 0, s, a);
   }
 
@@ -355,10 +348,10 @@ struct Impl {
             hipLaunchKernelGGL((k_tile_pull<ST, G, true, 256>), dim3(np), dim3(256), 0, s, a, t);
         });
         launch(pr, "tile_finish", s, [&] {
-          hipLaunchKernelGGL((k_tile_finish<ST, G, true>), dim3(nfin), dim3(256), 0, s, a, t);
+          hipLaunchKernelGGL((k_tile_finish<ST, G>), dim3(nfin), dim3(256), 0, s, a, t);
         });
         launch(pr, "tile_total", s, [&] {
-          hipLaunchKernelGGL((k_tile_total<ST, true>), dim3(1), dim3(256), 0, s, a, t, np, nfin, 0ull, 0ull);
+          hipLaunchKernelGGL(k_tile_total<ST>, dim3(1), dim3(256), 0, s, a, t, np, nfin);
         });
         return;
       }
@@ -520,6 +513,12 @@ daic_status check_opts(const daic_problem* p, const daic_run_opts* o) {
   return DAIC_OK;
 }
 
+void clear_radix(daic_problem* p, hipStream_t s) {
+  if (p->end.topk)
+    hipLaunchKernelGGL(k_fill<uint32_t>, dim3(grid_for(kRadixBins * kRadixCopies)), dim3(256), 0, s, p->a.rhist, 0u,
+                       (uint64_t)(kRadixBins * kRadixCopies));
+}
+
 // Dense rounds (pull over in-edges) for sum problems: builds the in-edge form
 // on first use and sets the direction rule of this run. DAIC_NO_PULL=1 turns
 // them off; DAIC_PULL_DIV (default 32) sets the fraction n/div of updating
@@ -531,8 +530,11 @@ void apply_run_opts(daic_problem* p, const daic_run_opts* o) {
 }
 
 daic_status dense_rounds_setup(daic_problem* p, const daic_run_opts* o, hipStream_t s) {
-  p->k_sel = 0;
-  p->pull_min = 0;
+  p->end = RoundEnd{};
+  // exact selections (also the learned rule's) are started by the round before
+  if (o->sched == DAIC_SCHED_TOPK_EXACT || o->sched == DAIC_SCHED_LEARNED)
+    p->end.topk = std::max<uint64_t>(1, (uint64_t)std::ceil(o->priority_fraction * (double)p->g->dev.n));
+  p->end.learned = o->sched == DAIC_SCHED_LEARNED ? 1 : 0;
   const bool sum = p->st == ST_F64 || p->st == ST_F32 || p->st == ST_F32K;
   const GraphDev& d = p->g->dev;
   // min and max problems take dense rounds through the tiled in-edges only
@@ -703,8 +705,8 @@ daic_status dense_rounds_setup(daic_problem* p, const daic_run_opts* o, hipStrea
   if (const char* e = std::getenv(sum ? "DAIC_PULL_DIV" : "DAIC_PULL_EDGE_DIV"))
     div = std::max<uint64_t>(1, std::strtoull(e, nullptr, 10));
   const uint64_t n = d.n;
-  p->k_sel = o->sched == DAIC_SCHED_ALL ? n : std::max<uint64_t>(1, (uint64_t)std::ceil(o->priority_fraction * (double)n));
-  p->pull_min = std::max<uint64_t>(1, ((sum ? n : d.m) + div - 1) / div);
+  p->end.k_sel = o->sched == DAIC_SCHED_ALL ? n : std::max<uint64_t>(1, (uint64_t)std::ceil(o->priority_fraction * (double)n));
+  p->end.pull_min = std::max<uint64_t>(1, ((sum ? n : d.m) + div - 1) / div);
   return DAIC_OK;
 }
 
@@ -891,7 +893,6 @@ daic_status daic_problem_create(const daic_graph* g, daic_op op, daic_g gk, doub
   GRAB(blk_large, uint32_t*, nb * 4);
   GRAB(blk_ties, uint32_t*, nb * 4);
   GRAB(rhist, uint32_t*, kRadixBins * kRadixCopies * 4);
-  GRAB(skeys, uint64_t*, kMaxSamples * 8);
   GRAB(off_small, uint64_t*, (nb + 1) * 8);
   GRAB(off_large, uint64_t*, (nb + 1) * 8);
   GRAB(off_ties, uint64_t*, (nb + 1) * 8);
@@ -1109,14 +1110,15 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
   rc = dense_rounds_setup(p, o, s);
   if (rc) return rc;
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(1), 0, s, p->a.ctl, o->eps, max_rounds);
+  clear_radix(p, s);
   ops.residual(p, s, 0);
   DAIC_HIP(hipEventRecord(p->ev0, s));
 
   const bool learned = o->sched == DAIC_SCHED_LEARNED;
   const bool use_graph = std::getenv("DAIC_NO_GRAPH") == nullptr;
   // Learned rounds rank by priority x sigmoid(score). Exact top-k is the
-  // fallback and the judge, decided on the device each round (k_learned_pre /
-  // k_learned_post): one exact round calibrates the priority realized per
+  // fallback and the judge, decided on the device at the end of each round
+  // (learned_post / learned_pre): one exact round calibrates the priority realized per
   // message, a learned round below 0.8 x that figure hands the next 4 rounds
   // back to exact selection, and every 16 learned rounds are followed by a
   // fresh calibration round. So learned rounds are captured like the others.
@@ -1128,11 +1130,8 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
   }
   auto one_round = [&]() {
     if (learned) {
-      hipLaunchKernelGGL(k_learned_pre, dim3(1), dim3(1), 0, s, p->a.ctl);
       learned_scores_enqueue(p, o->model, s);
       ops.round(p, o, s, sc, nullptr);
-      if (sum_state) hipLaunchKernelGGL(k_learned_post<true>, dim3(1), dim3(1), 0, s, p->a.ctl);
-      else hipLaunchKernelGGL(k_learned_post<false>, dim3(1), dim3(1), 0, s, p->a.ctl);
     } else {
       ops.round(p, o, s, nullptr, nullptr);
     }
@@ -1145,8 +1144,7 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
   key.seed = o->seed;
   key.K = K;
   key.stream = s;
-  key.k_sel = p->k_sel;
-  key.pull_min = p->pull_min;
+  key.end = p->end;
   key.score = sc;
   key.model = learned ? o->model : nullptr;
   key.model_version = learned ? learned_model_version(o->model) : 0;
@@ -1349,6 +1347,7 @@ daic_status daic_profile(daic_problem* p, const daic_run_opts* o, uint32_t cap, 
   rc = dense_rounds_setup(p, o, s);
   if (rc) return rc;
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(1), 0, s, p->a.ctl, o->eps, max_rounds);
+  clear_radix(p, s);
   ops.residual(p, s, 0);
   DAIC_HIP(hipStreamSynchronize(s));
   std::vector<daic_kernel_time> acc;
@@ -1388,6 +1387,9 @@ daic_status daic_profile(daic_problem* p, const daic_run_opts* o, uint32_t cap, 
       float ms = 0.f;
       DAIC_HIP(hipEventElapsedTime(&ms, r.a, r.b));
       total_ms += ms;
+      // the two kernels of a round's end are reported by what they did
+      if (!std::strcmp(r.name, "settle")) r.name = c.last_pull ? "pull_tile_finish" : "residual";
+      if (!std::strcmp(r.name, "total")) r.name = c.last_pull ? "pull_tile_total" : "residual_total";
       // kernels of the other direction return at once: not counted as
       // launches (after a dense round, k_pull_finish takes the residual's part)
       const bool is_push = !std::strncmp(r.name, "push_", 5), is_pull = !std::strncmp(r.name, "pull_", 5);
@@ -1441,6 +1443,7 @@ daic_status daic_run_progress(daic_problem* p, const daic_run_opts* o, uint64_t 
   double* dsum = nullptr;
   DAIC_HIP(hipMalloc(&dsum, sizeof(double)));
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(1), 0, s, p->a.ctl, o->eps, max_rounds);
+  clear_radix(p, s);
   ops.residual(p, s, 0);
   const uint32_t pg = (uint32_t)std::min<uint64_t>(2048, (n + 255) / 256);
   double sum = 0.0;
@@ -1498,6 +1501,7 @@ daic_status daic_select_frontier(daic_problem* p, const daic_run_opts* o, uint64
   void* sel;
   DAIC_HIP(hipMalloc(&sel, n));
   p->a.sel_out = static_cast<uint8_t*>(sel);
+  p->end = RoundEnd{};
   DAIC_HIP(hipMemsetAsync(sel, 0, n, s));
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(1), 0, s, p->a.ctl, 0.0, ~0ull);
   ops.residual(p, s, 0);

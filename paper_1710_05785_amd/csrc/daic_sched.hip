@@ -967,6 +967,7 @@ daic_status daic_trace_record(daic_problem* p, const daic_run_opts* o, uint32_t 
   DAIC_HIP(hipMalloc(&td.sel, R * S));
   LearnedOps lo = learned_ops(p);
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(1), 0, s, p->a.ctl, o->eps, R);
+  clear_radix(p, s);
   ops.residual(p, s, 0);
   uint64_t t = 0;
   hipError_t e = hipSuccess;

@@ -44,7 +44,6 @@ constexpr uint32_t kSmallMaxN = 16384;       // message bases of 8 bytes each: 1
 constexpr uint32_t kSmallMaxM = 1u << 18;    // in-edges at most (see small_applies)
 constexpr uint64_t kSmallStream = 3u << 19;  // bytes of in-neighbours and weights per round at most, for
                                              // rules whose general rounds have no threshold kernels
-constexpr uint32_t kSmallList = 64;          // threshold: candidates ranked directly
 constexpr uint32_t kSmallRounds = 4096;      // rounds per launch at most
 
 struct SmallArgs {
@@ -76,17 +75,6 @@ struct SmallArgs {
   uint32_t resume;           // continue the counters of the control block
 };
 
-// f(0), f(1), ..., f(N - 1) with constant arguments: the state's register
-// arrays are only ever indexed by constants (a loop with an exit would have
-// them moved as whole vectors).
-template <int N, int K = 0, typename F>
-__device__ __forceinline__ void small_each(const F& f) {
-  if constexpr (K < N) {
-    f(std::integral_constant<int, K>{});
-    small_each<N, K + 1>(f);
-  }
-}
-
 // Type of an LDS accumulator and the identity of its combination.
 template <int ST>
 struct SmallAcc {
@@ -96,115 +84,6 @@ struct SmallAcc {
 template <> struct SmallAcc<ST_F64> { using L = double; static constexpr L ident = 0.0; };
 template <> struct SmallAcc<ST_F32> { using L = double; static constexpr L ident = 0.0; };
 template <> struct SmallAcc<ST_F32K> { using L = double; static constexpr L ident = 0.0; };
-
-// z mod n for n < 2^14 by the reciprocal n_inv = floor((2^64 - 1) / n): the
-// quotient estimate is at most two below the true one.
-__device__ __forceinline__ uint32_t small_mod(uint64_t z, uint32_t n, uint64_t n_inv) {
-  uint64_t r = z - __umul64hi(z, n_inv) * n;
-  if (r >= n) r -= n;
-  if (r >= n) r -= n;
-  return (uint32_t)r;
-}
-
-struct SmallSelect {
-  uint32_t hist[2][256];
-  uint64_t list[kSmallList];
-  uint32_t count;
-  uint32_t digit, cnt, above;  // a pass's result
-  uint64_t tau;
-  uint32_t equal, rem;
-};
-
-// The rank-th largest of the workgroup's keys (key(u) for u < NK, valid(u)
-// telling whether it counts; 1 <= rank <= valid keys), 8 bits per pass from
-// the top: *equal keys have that value and *rem of them are within the rank.
-// The digit most lanes of a wave share is added to the histogram once (the
-// leading digits of priorities agree, and LDS atomics of one address take
-// turns); one wave scans the histogram (sixteen doing so would take the issue
-// slots of the CU four times over); a digit holding few keys ends the passes,
-// its keys ranked against each other by one wave.
-template <typename Key, int NK, typename KeyF, typename ValidF>
-__device__ __forceinline__ Key small_kth(SmallSelect& s, uint32_t rank, const KeyF& key, const ValidF& valid,
-                                         uint32_t* equal, uint32_t* rem) {
-  const uint32_t tid = threadIdx.x, lane = tid & 63;
-  if (tid < 256) s.hist[0][tid] = 0;
-  if (tid == 0) s.count = 0;
-  __syncthreads();
-  Key prefix = 0, mask = 0;
-  uint32_t left = rank, buf = 0;
-  for (int shift = (int)sizeof(Key) * 8 - 8;; shift -= 8) {
-    uint32_t* h = s.hist[buf];
-    small_each<NK>([&](auto u) {
-      const Key k = key(u);
-      bool on = valid(u) && (k & mask) == prefix;
-      const uint32_t d = (uint32_t)(k >> shift) & 255u;
-      const uint64_t live = __ballot(on);
-      if (live) {
-        const uint32_t d0 = __builtin_amdgcn_readlane(d, (uint32_t)__ffsll((unsigned long long)live) - 1);
-        const uint64_t same = __ballot(on && d == d0);
-        on = on && d != d0;
-        if (on || lane == 0) atomicAdd(&h[on ? d : d0], on ? 1u : (uint32_t)__popcll(same));
-        if (lane == 0 && on) atomicAdd(&h[d0], (uint32_t)__popcll(same));
-      }
-    });
-    __syncthreads();
-    if (tid < 64) {
-      // bins from the top: lane l holds bins 255 - 4l - q
-      uint32_t c[4], sum = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        c[q] = h[255 - 4 * lane - q];
-        sum += c[q];
-      }
-      uint32_t above = wave_incl_scan(sum) - sum;
-      if (above < left && left <= above + sum) {  // one lane
-        uint32_t q = 0;
-        while (q < 3 && above + c[q] < left) above += c[q++];
-        s.digit = 255 - 4 * lane - q;
-        s.cnt = q == 0 ? c[0] : q == 1 ? c[1] : q == 2 ? c[2] : c[3];
-        s.above = above;
-      }
-    } else if (tid < 320) {
-      s.hist[buf ^ 1][tid - 64] = 0;
-    }
-    __syncthreads();
-    const uint32_t cnt = s.cnt;
-    left -= s.above;
-    prefix |= (Key)s.digit << shift;
-    mask |= (Key)255 << shift;
-    if (shift == 0) {
-      *equal = cnt;
-      *rem = left;
-      return prefix;
-    }
-    if (cnt <= kSmallList) {
-      small_each<NK>([&](auto u) {
-        const Key k = key(u);
-        if (valid(u) && (k & mask) == prefix) s.list[atomicAdd(&s.count, 1u)] = (uint64_t)k;
-      });
-      __syncthreads();
-      if (tid < 64) {
-        const Key mine = (Key)s.list[min(lane, cnt - 1)];
-        uint32_t more = 0, same = 0;
-        for (uint32_t i = 0; i < cnt; ++i) {
-          const Key o = (Key)s.list[i];
-          more += o > mine ? 1u : 0u;
-          same += o == mine ? 1u : 0u;
-        }
-        if (lane < cnt && more < left && left <= more + same) {  // equal keys store the same values
-          s.tau = (uint64_t)mine;
-          s.equal = same;
-          s.rem = left - more;
-        }
-      }
-      __syncthreads();
-      *equal = s.equal;
-      *rem = s.rem;
-      return (Key)s.tau;
-    }
-    buf ^= 1;
-  }
-}
 
 // Combines message x into acc (sum, minimum or maximum).
 template <int ST>
@@ -313,7 +192,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
   constexpr L kIdent = SmallAcc<ST>::ident;
   __shared__ S base[NPT * kSmallThreads + 8];  // message bases; the sampled rule's keys before the claim
   __shared__ L heavy[kSmallMaxHeavy];          // sums of the heavy vertices
-  __shared__ SmallSelect sel;
+  __shared__ KthScratch sel;
   __shared__ double red_r[16];
   __shared__ uint32_t red_n[16];
   __shared__ double code_coef[kSmallDegs];
@@ -332,7 +211,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
     code_deg[i] = t.code_deg[i];
     code_coef[i] = t.code_coef[i];
   }
-  small_each<NPT>([&](auto k) {
+  unroll_each<NPT>([&](auto k) {
     v[k] = silent;
     dv[k] = silent;
     if constexpr (Tr<ST>::kahan) c[k] = 0.f;
@@ -368,13 +247,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const uint64_t i = (uint64_t)tx + (uint64_t)u * kSmallThreads;
-        at[u] = t.num[small_mod(splitmix64_at(t.seed, rounds * (uint64_t)t.S + i), n, t.n_inv)];
+        at[u] = t.num[mod_by_inverse(splitmix64_at(t.seed, rounds * (uint64_t)t.S + i), n, t.n_inv)];
       }
     }
     // A1: the residual of the state, and the stop rule
     double rp = 0.0;
     uint32_t np = 0;
-    small_each<NPT>([&](auto k) {
+    unroll_each<NPT>([&](auto k) {
       if constexpr (kSum) {
         const double x = fabs((double)dv[k]);
         rp += x;
@@ -408,19 +287,19 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
     uint32_t ties = 0, allow = ~0u;
     if (t.sched == DAIC_SCHED_TOPK_SAMPLED) {
       Key* keys = reinterpret_cast<Key*>(base);
-      small_each<NPT>([&](auto k) { keys[k * kSmallThreads + tx] = small_key<ST>(v[k], dv[k]); });
+      unroll_each<NPT>([&](auto k) { keys[k * kSmallThreads + tx] = small_key<ST>(v[k], dv[k]); });
       __syncthreads();
       Key ks[4];
-      small_each<4>([&](auto u) { ks[u] = keys[at[u]]; });
+      unroll_each<4>([&](auto u) { ks[u] = keys[at[u]]; });
       uint32_t equal, rem;
-      const Key tau = small_kth<Key, 4>(
+      const Key tau = block_kth<Key, 4>(
           sel, t.rank, [&](auto u) { return ks[u]; }, [&](auto u) { return tid + u * kSmallThreads < t.S; }, &equal,
           &rem);
       if (tau != 0) lo = tau;  // no positive sample: every pending vertex
     } else if (t.sched == DAIC_SCHED_TOPK_EXACT) {
       if (pending > t.k) {
         uint32_t equal, rem;
-        lo = small_kth<Key, NPT>(
+        lo = block_kth<Key, NPT>(
             sel, (uint32_t)t.k, [&](auto u) { return small_key<ST>(v[u], dv[u]); },
             [&](auto u) { return small_key<ST>(v[u], dv[u]) != 0; }, &equal, &rem);
         if (equal != rem) {
@@ -431,7 +310,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
           uint32_t* wsum = sel.hist[0];
           if (tid < 512) bits[tid] = 0;
           __syncthreads();
-          small_each<NPT>([&](auto k) {
+          unroll_each<NPT>([&](auto k) {
             if (small_key<ST>(v[k], dv[k]) == veto) {  // positive: a vertex
               const uint32_t j = (t.id + k * kSmallThreads)[tx];
               atomicOr(&bits[j >> 5], 1u << (j & 31));
@@ -446,7 +325,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
           for (uint32_t w = 0; w < wave; ++w) before += wsum[w];
           if (tid < 512) bits[512 + tid] = before;
           __syncthreads();
-          small_each<NPT>([&](auto k) {
+          unroll_each<NPT>([&](auto k) {
             if (small_key<ST>(v[k], dv[k]) == veto) {
               const uint32_t j = (t.id + k * kSmallThreads)[tx];
               const uint32_t r = bits[512 + (j >> 5)] + (uint32_t)__popc(bits[j >> 5] & ((1u << (j & 31)) - 1u));
@@ -459,7 +338,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
       const uint32_t rr_lo = (uint32_t)(rounds % ((a.n + a.rr_chunk - 1) / a.rr_chunk) * a.rr_chunk);
       const uint32_t rr_len = (uint32_t)min((uint64_t)n, a.rr_chunk);
       allow = 0;
-      small_each<NPT>([&](auto k) {
+      unroll_each<NPT>([&](auto k) {
         if ((t.id + k * kSmallThreads)[tx] - rr_lo < rr_len) allow |= 1u << k;
       });
     }
@@ -468,7 +347,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
     // A3 + A4: claim, fold, message base
     if (kSum && !Tr<ST>::kahan && t.sched == DAIC_SCHED_ALL && a.alpha_pv == nullptr) {
       // as below with every vertex taken: one without a delta adds and sends 0
-      small_each<NPT>([&](auto k) {
+      unroll_each<NPT>([&](auto k) {
         const uint32_t ci = code[k / 2] >> (k % 2 * 16) & 0xFFFFu;
         const S delta = dv[k];
         v[k] += delta;
@@ -479,7 +358,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
         if constexpr (k % 2 == 1) asm volatile("" ::: "memory");  // the next operands stay behind (registers)
       });
     } else {
-      small_each<NPT>([&](auto k) {
+      unroll_each<NPT>([&](auto k) {
         const uint32_t ci = code[k / 2] >> (k % 2 * 16) & 0xFFFFu;
         const uint32_t dg = code_deg[ci];
         double cf = 0.0;
@@ -521,7 +400,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
     // A5: this thread's vertices, then its pieces of the heavy ones
     SmallWalk<ST, G> walk;
     walk.start(t, t.wave_off[wave]);
-    small_each<NPT>([&](auto k) {
+    unroll_each<NPT>([&](auto k) {
       const uint32_t groups = t.len[wave * 16 + k];
       if (groups) small_receive<ST>(walk.slice(base, groups), v[k], dv[k]);
     });
@@ -537,7 +416,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
         }
       }
       __syncthreads();
-      small_each<(NPT < kSmallMaxHeavy / kSmallThreads ? NPT : kSmallMaxHeavy / kSmallThreads)>([&](auto k) {
+      unroll_each<(NPT < kSmallMaxHeavy / kSmallThreads ? NPT : kSmallMaxHeavy / kSmallThreads)>([&](auto k) {
         if (k * kSmallThreads + tx < t.n_heavy) {
           small_receive<ST>(heavy[k * kSmallThreads + tx], v[k], dv[k]);
           heavy[k * kSmallThreads + tx] = kIdent;  // for the next round (its pieces come after barriers)
@@ -548,7 +427,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
   }
 
   // the state, and the run's counters
-  small_each<NPT>([&](auto k) {
+  unroll_each<NPT>([&](auto k) {
     const uint32_t r = k * kSmallThreads + tid;
     if (r < n) {
       const uint32_t j = t.id[r];

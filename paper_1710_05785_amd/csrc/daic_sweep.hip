@@ -803,6 +803,7 @@ daic_status sweep_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats
   const uint32_t K = P * std::max<uint32_t>(1, (want + P - 1) / P);
   const uint64_t max_rounds = o->max_rounds ? o->max_rounds : ~0ull;
 
+  p->end = RoundEnd{};
   DAIC_HIP(hipMemsetAsync(w.a.mu2, 0, 2 * n * sweep_state_size(p->st), s));
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(1), 0, s, p->a.ctl, o->eps, max_rounds);
   ops.residual(p, s, 0);

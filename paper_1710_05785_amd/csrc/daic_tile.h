@@ -257,11 +257,10 @@ __global__ __launch_bounds__(NT) void k_tile_pull(KArgs a, TileArgs t) {
 // Targets of split partitions: a work item is 256 consecutive targets of one
 // split partition; their slots are added in tile order, 16 loads in flight.
 template <int ST, int G, bool FUSED>
-__global__ __launch_bounds__(256) void k_tile_finish(KArgs a, TileArgs t) {
+__device__ __forceinline__ void tile_finish_block(const KArgs& a, const TileArgs& t, uint32_t nblocks) {
   using S = typename Tr<ST>::S;
   if constexpr (Tr<ST>::sum) {
     Ctl* ctl = a.ctl;
-    if (ctl_halted(ctl) || (!FUSED && !ctl->last_pull)) return;
     const bool odd = FUSED && ((ctl->rounds - ctl->fuse_base) & 1) != 0;
     S* mu_out = static_cast<S*>(odd ? a.mu_pi : a.mu_pi2);
     const SlotT<ST>* pbuf = reinterpret_cast<const SlotT<ST>*>(t.pbuf);
@@ -269,7 +268,7 @@ __global__ __launch_bounds__(256) void k_tile_finish(KArgs a, TileArgs t) {
     const uint32_t kChunks = t.tw / 256;
     double r_part = 0.0;
     uint64_t act = 0, pushed = 0;
-    for (uint64_t item = blockIdx.x; item < t.n_split * kChunks; item += gridDim.x) {
+    for (uint64_t item = blockIdx.x; item < t.n_split * kChunks; item += nblocks) {
       const uint64_t sp = item / kChunks;
       const uint32_t chunk = (uint32_t)(item % kChunks);
       const uint32_t part = t.split_part[sp], k0 = t.split_slot[sp], k1 = t.split_slot[sp + 1];
@@ -300,16 +299,22 @@ __global__ __launch_bounds__(256) void k_tile_finish(KArgs a, TileArgs t) {
   }
 }
 
+// (fused rounds; the others' finishing is a part of k_settle)
+template <int ST, int G>
+__global__ __launch_bounds__(256) void k_tile_finish(KArgs a, TileArgs t) {
+  if (ctl_halted(a.ctl)) return;
+  tile_finish_block<ST, G, true>(a, t, gridDim.x);
+}
+
 // The round's totals (one block): partials of np k_tile_pull and nf
 // k_tile_finish workgroups in a fixed order; residual, counters, round count
 // and stop rule as k_fused_finish sets them (FUSED), or residual, pending
 // count, round count, stop rule and next direction as k_pull_finish does.
 template <int ST, bool FUSED>
-__global__ __launch_bounds__(256) void k_tile_total(KArgs a, TileArgs t, uint32_t np, uint32_t nf, uint64_t k_sel,
-                                                    uint64_t pull_min) {
+__device__ __forceinline__ void tile_totals(const KArgs& a, const TileArgs& t, uint32_t np, uint32_t nf,
+                                            const RoundEnd& e) {
   if constexpr (Tr<ST>::sum || !FUSED) {
     Ctl* ctl = a.ctl;
-    if (ctl_halted(ctl) || (!FUSED && !ctl->last_pull)) return;
     double rr = 0.0;
     uint64_t aa = 0, ps = 0;
     // eight partials per thread at a time, their loads in flight together
@@ -356,10 +361,17 @@ __global__ __launch_bounds__(256) void k_tile_total(KArgs a, TileArgs t, uint32_
         const bool done = Tr<ST>::sum ? (rr <= ctl->eps || nn == 0) : nn == 0;
         ctl->done = done ? 1u : 0u;
         ctl->stop = (!done && ctl->rounds >= ctl->max_rounds) ? 1u : 0u;
-        ctl->pull = next_is_dense<ST>(nn, rr, k_sel, pull_min);
+        ctl->pull = next_is_dense<ST>(nn, rr, e.k_sel, e.pull_min);
+        round_end<ST>(ctl, 1, e);
       }
     }
   }
+}
+
+template <int ST>
+__global__ __launch_bounds__(256) void k_tile_total(KArgs a, TileArgs t, uint32_t np, uint32_t nf) {
+  if (ctl_halted(a.ctl)) return;
+  tile_totals<ST, true>(a, t, np, nf, RoundEnd{});
 }
 
 // ---------------------------------------------------------------------------
@@ -494,14 +506,12 @@ __global__ __launch_bounds__(NT) void k_tile_pull_mm(KArgs a, TileArgs t) {
 
 // Targets of split partitions: their slots combined in tile order, then
 // taken into dv as above.
-template <int ST, int G>
-__global__ __launch_bounds__(256) void k_tile_finish_mm(KArgs a, TileArgs t) {
+template <int ST>
+__device__ __forceinline__ void tile_finish_block_mm(const KArgs& a, const TileArgs& t, uint32_t nblocks) {
   if constexpr (!Tr<ST>::sum) {
     using S = typename Tr<ST>::S;
     using M = TileMM<ST>;
     using L = typename M::L;
-    Ctl* ctl = a.ctl;
-    if (ctl_halted(ctl) || !ctl->last_pull) return;
     const L* pbuf = reinterpret_cast<const L*>(t.pbuf);
     const S* v = static_cast<const S*>(a.v);
     const S* dv = static_cast<const S*>(a.dv);
@@ -509,7 +519,7 @@ __global__ __launch_bounds__(256) void k_tile_finish_mm(KArgs a, TileArgs t) {
     const uint32_t kChunks = t.tw / 256;
     double r_part = 0.0;
     uint64_t act = 0;
-    for (uint64_t item = blockIdx.x; item < t.n_split * kChunks; item += gridDim.x) {
+    for (uint64_t item = blockIdx.x; item < t.n_split * kChunks; item += nblocks) {
       const uint64_t sp = item / kChunks;
       const uint32_t chunk = (uint32_t)(item % kChunks);
       const uint32_t part = t.split_part[sp], k0 = t.split_slot[sp], k1 = t.split_slot[sp + 1];
@@ -537,6 +547,31 @@ __global__ __launch_bounds__(256) void k_tile_finish_mm(KArgs a, TileArgs t) {
       t.spart_p[blockIdx.x] = 0;
     }
   }
+}
+
+// The end of a round in either direction, in two launches (each of the four
+// kernels they replace returned at once in the rounds of the other direction,
+// at 4-6 us a launch): k_settle finishes the split partitions of a dense round
+// (its first nfin workgroups), or takes the residual's partials after a push
+// round; k_total adds up the partials of either.
+template <int ST, int G>
+__global__ __launch_bounds__(256) void k_settle(KArgs a, TileArgs t, uint32_t nfin) {
+  const Ctl* ctl = a.ctl;
+  if (ctl_halted(ctl)) return;
+  if (ctl->last_pull) {
+    if (blockIdx.x >= nfin) return;
+    if constexpr (Tr<ST>::sum) tile_finish_block<ST, G, false>(a, t, nfin);
+    else tile_finish_block_mm<ST>(a, t, nfin);
+  } else if (blockIdx.x < a.blocks) {
+    residual_block<ST>(a);
+  }
+}
+
+template <int ST>
+__global__ __launch_bounds__(256) void k_total(KArgs a, TileArgs t, uint32_t np, uint32_t nf, RoundEnd e) {
+  if (ctl_halted(a.ctl)) return;
+  if (a.ctl->last_pull) tile_totals<ST, false>(a, t, np, nf, e);
+  else residual_totals<ST>(a, 1, e);
 }
 
 }  // namespace daic
