@@ -84,6 +84,34 @@ __device__ __forceinline__ T block_sum_waves(T x) {
   return t;
 }
 
+// Sums of N integers and one double over a block of NW waves, all in one
+// exchange (every thread must call it; the totals are returned to all).
+template <int NW, int N>
+__device__ __forceinline__ void block_sums(uint64_t (&x)[N], double& d) {
+  __shared__ uint64_t s_x[NW][N];
+  __shared__ double s_d[NW];
+  const uint32_t wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = wave_sum(x[i]);
+  d = wave_sum(d);
+  if (lane_id() == 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) s_x[wave][i] = x[i];
+    s_d[wave] = d;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    x[i] = s_x[0][i];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) x[i] += s_x[w][i];
+  }
+  d = s_d[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) d += s_d[w];
+  __syncthreads();
+}
+
 // The out-edges of rows [0, n) of a 32-bit CSR offset array, four rows to a
 // wave: a group of 16 lanes per row with the row's edges strided over it
 // (most rows of power-law graphs hold a few dozen edges, which a whole wave

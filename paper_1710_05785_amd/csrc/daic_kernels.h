@@ -6,7 +6,6 @@
 //   A3+A4 k_claim           : select, claim dv_j, fold v_j (+)= delta, compute
 //                             the message base mu_j, compact into degree bins
 //                             (sparse rounds) or publish mu_j (dense rounds)
-//   k_bin_scan              : prefix of the per-block bin counts
 //   A5 k_push               : atomic (+) of g(mu_j) into dv_k for every out-edge
 //                             (small and large bins in one launch)
 //      dense rounds         : every target combines its in-neighbours' bases,
@@ -62,13 +61,12 @@ struct KArgs {
   uint32_t* large_chunk;
   void* large_mu;
   const uint64_t* large_off;  // [blocks+1]
-  uint32_t* blk_small;      // per-block counts of this round
+  uint32_t* blk_small;      // per-block counts of this round (kMaxScanBlocks each, 0 beyond the blocks)
   uint32_t* blk_large;
-  uint64_t* off_small;      // [blocks+1] prefix of blk_small
-  uint64_t* off_large;      // [blocks+1] prefix of blk_large
   uint64_t* blk_act;        // per-block activations / pushed edges (all, large bin)
   uint64_t* blk_push;
   uint64_t* blk_push_large;
+  double* blk_gain;         // learned runs: per-block priority realized by the selected vertices
   uint32_t* blk_ties;       // exact top-k: keys equal to tau per block
   uint32_t* rhist;          // exact top-k: radix histogram (kRadixCopies x kRadixBins counters)
   uint64_t* off_ties;       // exclusive prefix of blk_ties
@@ -193,7 +191,7 @@ __device__ __forceinline__ uint64_t row_at(const void* row, uint64_t j) {
 }
 
 // Index b with off[b] <= i < off[b+1] (off has nb+1 entries, off[0] = 0).
-__device__ __forceinline__ uint32_t find_block(const uint64_t* off, uint32_t nb, uint64_t i) {
+__device__ __forceinline__ uint32_t find_block(const uint32_t* off, uint32_t nb, uint32_t i) {
   uint32_t lo = 0, hi = nb;  // invariant: off[lo] <= i < off[hi]
   while (hi - lo > 1) {
     uint32_t mid = (lo + hi) >> 1;
@@ -336,11 +334,11 @@ __device__ __forceinline__ void residual_block(const KArgs& a) {
       }
     }
   }
-  r = block_sum256(r);
-  cnt = block_sum256(cnt);
+  uint64_t x[1] = {cnt};
+  block_sums<4>(x, r);
   if (threadIdx.x == 0) {
     a.part_r[b] = r;
-    a.part_n[b] = cnt;
+    a.part_n[b] = x[0];
   }
 }
 
@@ -423,6 +421,67 @@ __device__ __forceinline__ void learned_post(Ctl* ctl) {
   }
 }
 
+// The work counters of the round's claim: a thread's share of its per-block
+// counts (a block of 256 threads; unconditional loads, so that they and the
+// residual's are in flight together), and the totals into the control block.
+struct ClaimCounts {
+  uint64_t x[5] = {0, 0, 0, 0, 0};  // updates, messages, those of the large bin, items of the two bins
+  double gain = 0.0;
+};
+
+__device__ __forceinline__ ClaimCounts claim_counts(const KArgs& a) {
+  static_assert(kMaxScanBlocks % 256 == 0, "an equal number of blocks per thread");
+  constexpr uint32_t PER = kMaxScanBlocks / 256;
+  const bool learned = a.last_upd != nullptr;
+  uint64_t y[PER][5];
+  double g[PER];
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint32_t i = min(threadIdx.x + 256 * u, a.blocks - 1);
+    y[u][0] = a.blk_act[i];
+    y[u][1] = a.blk_push[i];
+    y[u][2] = a.blk_push_large[i];
+    y[u][3] = a.blk_small[i];
+    y[u][4] = a.blk_large[i];
+    g[u] = learned ? a.blk_gain[i] : 0.0;
+  }
+  ClaimCounts c;
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u)
+    if (threadIdx.x + 256 * u < a.blocks) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) c.x[i] += y[u][i];
+      c.gain += g[u];
+    }
+  return c;
+}
+
+// One thread, with the block's totals.
+__device__ __forceinline__ void store_counts(const KArgs& a, const uint64_t* x, double gain) {
+  Ctl* ctl = a.ctl;
+  ctl->n_small = x[3];
+  ctl->n_large = x[4];
+  if (a.last_upd != nullptr) ctl->l_gain = gain;
+  ctl->activations += x[0];
+  ctl->pushed += x[1];
+  ctl->pushed_large += x[2];
+  ctl->round_act = x[0];
+  ctl->round_pushed = x[1];
+  ctl->round_pushed_large = x[2];
+}
+
+__device__ __forceinline__ void round_counters(const KArgs& a) {
+  ClaimCounts c = claim_counts(a);
+  block_sums<4>(c.x, c.gain);
+  if (threadIdx.x == 0) store_counts(a, c.x, c.gain);
+}
+
+// The counters alone: the claim that opens fused dense rounds.
+static __global__ __launch_bounds__(256) void k_counters(KArgs a) {
+  if (ctl_halted(a.ctl)) return;
+  round_counters(a);
+}
+
 // One thread, after the residual, the counters and the stop flags of a
 // finished round (count_round 1) or of the run's starting state (0).
 template <int ST>
@@ -438,26 +497,29 @@ __device__ __forceinline__ void round_end(Ctl* ctl, int count_round, const Round
 template <int ST>
 __device__ __forceinline__ void residual_totals(const KArgs& a, int count_round, const RoundEnd& e) {
   Ctl* ctl = a.ctl;
-  double rr = 0.0;
-  uint64_t nn = 0;
-  for (uint32_t i0 = threadIdx.x; i0 < a.blocks; i0 += 2048) {
-    double pr[8];
-    uint64_t pn[8];
+  constexpr uint32_t PER = kMaxScanBlocks / 256;
+  double pr[PER];
+  uint64_t pn[PER];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const uint32_t i = min(i0 + 256 * u, a.blocks - 1);
-      pr[u] = a.part_r[i];
-      pn[u] = a.part_n[i];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (i0 + 256 * u >= a.blocks) break;
-      rr += pr[u];
-      nn += pn[u];
-    }
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint32_t i = min(threadIdx.x + 256 * u, a.blocks - 1);
+    pr[u] = a.part_r[i];
+    pn[u] = a.part_n[i];
   }
-  rr = block_sum256(rr);
-  nn = block_sum256(nn);
+  ClaimCounts c;
+  if (count_round) c = claim_counts(a);
+  double rr = 0.0;
+  uint64_t x[6] = {0, c.x[0], c.x[1], c.x[2], c.x[3], c.x[4]};
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u)
+    if (threadIdx.x + 256 * u < a.blocks) {
+      rr += pr[u];
+      x[0] += pn[u];
+    }
+  block_sums<4>(x, rr);
+  if (a.last_upd != nullptr) c.gain = block_sum256(c.gain);  // uniform
+  const uint64_t nn = x[0];
+  if (threadIdx.x == 0 && count_round) store_counts(a, x + 1, c.gain);
   if (threadIdx.x == 0) {
     if constexpr (Tr<ST>::sum) ctl->r = rr; else ctl->r = (double)nn;
     ctl->pending = nn;
@@ -604,6 +666,33 @@ __device__ __forceinline__ Key block_kth(KthScratch& s, uint32_t rank, const Key
   }
 }
 
+// The rank-th largest of count sampled keys, four per thread, when `pending`
+// of n vertices have a positive one. Where the rank may lie among the zeros (a
+// narrow frontier) the positive samples are counted first: the common digits
+// of the zeros would take every pass to the end.
+template <typename Key>
+__device__ __forceinline__ Key block_kth_sampled(KthScratch& s, uint32_t rank, uint32_t count, uint64_t pending,
+                                                 uint64_t n, const Key (&key)[4]) {
+  const uint32_t tid = threadIdx.x;
+  uint32_t equal, rem;
+  if ((double)pending * count > 2.0 * (double)rank * (double)n)
+    return block_kth<Key, 4>(
+        s, rank, [&](auto u) { return key[u]; }, [&](auto u) { return tid + u * 1024 < count; }, &equal, &rem);
+  uint32_t mine = 0;
+  unroll_each<4>([&](auto u) { mine += tid + u * 1024 < count && key[u] != 0 ? 1u : 0u; });
+  mine = wave_sum(mine);
+  if (lane_id() == 0) s.hist[1][tid >> 6] = mine;
+  __syncthreads();
+  uint32_t positive = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) positive += s.hist[1][w];
+  __syncthreads();
+  if (positive < rank) return 0;
+  return block_kth<Key, 4>(
+      s, rank, [&](auto u) { return key[u]; }, [&](auto u) { return tid + u * 1024 < count && key[u] != 0; }, &equal,
+      &rem);
+}
+
 // ---------------------------------------------------------------------------
 // A2 (sampled): threshold = the rank-th largest of S sampled keys; a
 // threshold of 0 (no positive sample) selects every pending vertex. One
@@ -631,9 +720,7 @@ __global__ __launch_bounds__(1024) void k_sample(KArgs a, uint32_t S_n, uint32_t
   Key key[4];
 #pragma unroll
   for (uint32_t u = 0; u < 4; ++u) key[u] = prio_key<ST>(v[u], dv[u]);
-  uint32_t equal, rem;
-  const Key tau = block_kth<Key, 4>(
-      scratch, rank, [&](auto u) { return key[u]; }, [&](auto u) { return tid + u * 1024 < S_n; }, &equal, &rem);
+  const Key tau = block_kth_sampled<Key>(scratch, rank, S_n, ctl->pending, a.n, key);
   if (tid == 0) {
     ctl->sel_mode = tau == 0 ? 0u : 1u;
     ctl->tau = (uint64_t)tau;
@@ -949,6 +1036,7 @@ __global__ __launch_bounds__(256) void k_claim(KArgs a) {
   S* large_mu = static_cast<S*>(a.large_mu);
   const uint64_t large_base = DRY ? 0 : a.large_off[b];
   const bool pull = !DRY && ctl->pull != 0;
+  if (!DRY && b == 0 && threadIdx.x == 0) ctl->last_pull = pull ? 1u : 0u;
   uint64_t ties_seen = 0, n_small = 0, n_large = 0, act = 0, pushed = 0, pushed_large = 0;
   double gain = 0.0;  // learned runs (update rounds tracked): priority realized by the selected vertices
   const bool track = !DRY && a.last_upd != nullptr;
@@ -1109,13 +1197,12 @@ __global__ __launch_bounds__(256) void k_claim(KArgs a) {
     pushed_large += (send && deg > kSmallMaxDeg) ? deg : 0;
   }
   if constexpr (!DRY) {
-    act = block_sum256(act);
-    pushed = block_sum256(pushed);
-    pushed_large = block_sum256(pushed_large);
-    if (track) {  // kernel-uniform; the residual's partial slots are free until the round's residual
-      gain = block_sum256(gain);
-      if (threadIdx.x == 0) a.part_r[b] = gain;
-    }
+    uint64_t x[3] = {act, pushed, pushed_large};
+    block_sums<4>(x, gain);
+    act = x[0];
+    pushed = x[1];
+    pushed_large = x[2];
+    if (track && threadIdx.x == 0) a.blk_gain[b] = gain;
     if (threadIdx.x == 0) {
       a.blk_small[b] = (uint32_t)n_small;
       a.blk_large[b] = (uint32_t)n_large;
@@ -1126,126 +1213,83 @@ __global__ __launch_bounds__(256) void k_claim(KArgs a) {
   }
 }
 
-// Prefix of the bin counts and the round's work counters (one block of 1024
-// threads, two per-block entries per thread: every load is issued before any
-// scan step, so the kernel pays one memory round trip).
-static_assert(kMaxScanBlocks <= 2048, "k_bin_scan takes two per-block entries per thread");
-static __global__ __launch_bounds__(1024) void k_bin_scan(KArgs a) {
-  Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl)) return;
-  const uint32_t pull = ctl->pull;
-  const uint32_t nb = a.blocks, tid = threadIdx.x, i0 = 2 * tid, i1 = 2 * tid + 1;
-  const uint32_t lane = lane_id(), wave = tid >> 6;
-  const bool learned = a.last_upd != nullptr;  // learned runs: the realized priority, summed in a fixed order
-  uint32_t bs[2] = {0, 0}, bl[2] = {0, 0};
-  uint64_t act = 0, push = 0, pl = 0;
-  double g = 0.0;
+// ---------------------------------------------------------------------------
+// A5: the messages of a push round. Every workgroup of 256 threads forms the
+// prefix of the claim's per-block counts in LDS for itself (two loads per
+// thread and bin; a one-workgroup kernel that did it took 7 us of every
+// round, and items then searched it in memory, eleven loads deep); half of
+// its waves take the small bin (out-degree 1..32), 64 items each with their
+// concatenated edges spread over the lanes, so lanes stay busy whatever the
+// degree mix and column reads stay contiguous; the others the large bin, one
+// item of up to kChunk consecutive out-edges at a time.
+// ---------------------------------------------------------------------------
+template <typename S>
+struct PushShared {
+  uint32_t off_small[kMaxScanBlocks + 1], off_large[kMaxScanBlocks + 1];
+  uint32_t wave_sum[2][4];
+  struct {
+    uint64_t beg[64];
+    S mu[64];
+    uint32_t excl[64];
+    uint8_t owner[64 * kSmallMaxDeg];
+  } wave[4];
+};
+
+// Exclusive prefix of the per-block counts (kMaxScanBlocks of them, 0 beyond
+// the claim's blocks) into LDS (off[blocks] = total).
+__device__ __forceinline__ void push_prefix(const uint32_t* count, uint32_t nb, uint32_t* off, uint32_t* wave_sum) {
+  constexpr uint32_t PER = kMaxScanBlocks / 256;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6;
+  uint32_t x[PER], sum = 0;
 #pragma unroll
-  for (uint32_t u = 0; u < 2; ++u) {
-    const uint32_t i = i0 + u;
-    if (i < nb) {
-      bs[u] = a.blk_small[i];
-      bl[u] = a.blk_large[i];
-      act += a.blk_act[i];
-      push += a.blk_push[i];
-      pl += a.blk_push_large[i];
-      if (learned) g += a.part_r[i];
-    }
+  for (uint32_t u = 0; u < PER; u += 4) {
+    const uint4 y = reinterpret_cast<const uint4*>(count)[tid * (PER / 4) + u / 4];
+    x[u] = y.x;
+    x[u + 1] = y.y;
+    x[u + 2] = y.z;
+    x[u + 3] = y.w;
   }
-  const uint64_t xs = (uint64_t)bs[0] + bs[1], xl = (uint64_t)bl[0] + bl[1];
-  uint64_t ss = xs, sl = xl;  // wave inclusive scans
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t ys = __shfl_up(ss, d, 64), yl = __shfl_up(sl, d, 64);
-    if (lane >= (uint32_t)d) {
-      ss += ys;
-      sl += yl;
-    }
-  }
-  act = wave_sum(act);
-  push = wave_sum(push);
-  pl = wave_sum(pl);
-  g = wave_sum(g);
-  __shared__ uint64_t w_s[16], w_l[16], w_a[16], w_p[16], w_pl[16];
-  __shared__ double w_g[16];
-  if (lane == 63) {
-    w_s[wave] = ss;
-    w_l[wave] = sl;
-    w_a[wave] = act;
-    w_p[wave] = push;
-    w_pl[wave] = pl;
-    w_g[wave] = g;
-  }
+  for (uint32_t u = 0; u < PER; ++u) sum += x[u];
+  const uint32_t incl = wave_incl_scan(sum);
+  if (lane_id() == 63) wave_sum[wave] = incl;
   __syncthreads();
-  if (!pull) {  // the bins feed the push kernels only
-    uint64_t os = 0, ol = 0;
-    for (uint32_t w = 0; w < wave; ++w) {
-      os += w_s[w];
-      ol += w_l[w];
-    }
-    const uint64_t es = os + ss - xs, el = ol + sl - xl;
-    if (i0 < nb) {
-      a.off_small[i0] = es;
-      a.off_large[i0] = el;
-    }
-    if (i1 < nb) {
-      a.off_small[i1] = es + bs[0];
-      a.off_large[i1] = el + bl[0];
-    }
+  uint32_t at = incl - sum;
+#pragma unroll
+  for (uint32_t w = 0; w < 3; ++w) at += w < wave ? wave_sum[w] : 0u;
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint32_t i = tid * PER + u;
+    if (i <= nb) off[i] = at;
+    at += x[u];
   }
-  if (tid == 0) {
-    uint64_t ts = 0, tl = 0, ta = 0, tp = 0, tpl = 0;
-    double tg = 0.0;
-    for (int w = 0; w < 16; ++w) {
-      ts += w_s[w];
-      tl += w_l[w];
-      ta += w_a[w];
-      tp += w_p[w];
-      tpl += w_pl[w];
-      tg += w_g[w];
-    }
-    ctl->last_pull = pull;
-    if (!pull) {
-      a.off_small[nb] = ts;
-      a.off_large[nb] = tl;
-    }
-    ctl->n_small = pull ? 0 : ts;
-    ctl->n_large = pull ? 0 : tl;
-    if (learned) ctl->l_gain = tg;
-    ctl->activations += ta;
-    ctl->pushed += tp;
-    ctl->pushed_large += tpl;
-    ctl->round_act = ta;
-    ctl->round_pushed = tp;
-    ctl->round_pushed_large = tpl;
-  }
+  if (tid == 255 && nb == kMaxScanBlocks) off[nb] = at;
 }
 
-// ---------------------------------------------------------------------------
-// A5, small bin (out-degree 1..32): one wave (= one block of 64) takes 64
-// items and spreads their concatenated edges over its lanes, so lanes stay
-// busy whatever the degree mix and column reads stay contiguous.
-// ---------------------------------------------------------------------------
+// LDS of one wave written by it is read by it: only the order counts.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int ST, int G, typename RowT>
-__device__ __forceinline__ void push_small_items(const KArgs& a, uint64_t bid, uint64_t nb) {
+__device__ __forceinline__ void push_small_items(const KArgs& a, PushShared<typename Tr<ST>::S>& sh, uint32_t bid,
+                                                 uint32_t nb) {
   using S = typename Tr<ST>::S;
-  Ctl* ctl = a.ctl;
-  const uint64_t total = ctl->n_small;
-  __shared__ uint8_t owner[64 * kSmallMaxDeg];
-  __shared__ uint32_t s_excl[64];
-  __shared__ uint64_t s_beg[64];
-  __shared__ S s_mu[64];
-  const uint32_t lane = threadIdx.x;
+  const uint32_t total = sh.off_small[a.blocks];
+  auto& w = sh.wave[threadIdx.x >> 6];
+  const uint32_t lane = threadIdx.x & 63;
   const S* small_mu = static_cast<const S*>(a.small_mu);
   for (uint64_t g = bid; g * 64 < total; g += nb) {
-    const uint64_t i = g * 64 + lane;
+    const uint32_t i = (uint32_t)g * 64 + lane;
     uint32_t deg = 0;
     uint64_t beg = 0;
     S mu{};
     if (i < total) {
-      uint32_t blk = find_block(a.off_small, a.blocks, i);
-      uint64_t idx = (uint64_t)blk * a.per_block + (i - a.off_small[blk]);
-      uint32_t vid = a.small_vid[idx];
+      const uint32_t blk = find_block(sh.off_small, a.blocks, i);
+      const uint64_t idx = (uint64_t)blk * a.per_block + (i - sh.off_small[blk]);
+      const uint32_t vid = a.small_vid[idx];
       mu = small_mu[idx];
       beg = row_at<RowT>(a.row, vid);
       deg = (uint32_t)(row_at<RowT>(a.row, vid + 1) - beg);
@@ -1253,48 +1297,55 @@ __device__ __forceinline__ void push_small_items(const KArgs& a, uint64_t bid, u
     const uint32_t incl = wave_incl_scan(deg);
     const uint32_t excl = incl - deg;
     const uint32_t E = __shfl(incl, 63, 64);
-    s_excl[lane] = excl;
-    s_beg[lane] = beg;
-    s_mu[lane] = mu;
-    for (uint32_t k = 0; k < deg; ++k) owner[excl + k] = (uint8_t)lane;
-    __syncthreads();
+    w.excl[lane] = excl;
+    w.beg[lane] = beg;
+    w.mu[lane] = mu;
+    for (uint32_t k = 0; k < deg; ++k) w.owner[excl + k] = (uint8_t)lane;
+    wave_lds_sync();
     for (uint32_t e = lane; e < E; e += 64) {
-      const uint32_t o = owner[e];
-      push_edge<ST, G>(a, s_beg[o] + (e - s_excl[o]), s_mu[o]);
+      const uint32_t o = w.owner[e];
+      push_edge<ST, G>(a, w.beg[o] + (e - w.excl[o]), w.mu[o]);
     }
-    __syncthreads();
+    wave_lds_sync();
   }
 }
 
-// A5, large bin: one wave per item of up to kChunk consecutive out-edges.
 template <int ST, int G, typename RowT>
-__device__ __forceinline__ void push_large_items(const KArgs& a, uint64_t bid, uint64_t nb) {
+__device__ __forceinline__ void push_large_items(const KArgs& a, const PushShared<typename Tr<ST>::S>& sh,
+                                                 uint32_t bid, uint32_t nb) {
   using S = typename Tr<ST>::S;
-  Ctl* ctl = a.ctl;
-  const uint64_t total = ctl->n_large;
+  const uint32_t total = sh.off_large[a.blocks];
   const S* large_mu = static_cast<const S*>(a.large_mu);
   for (uint64_t i = bid; i < total; i += nb) {
-    uint32_t blk = find_block(a.off_large, a.blocks, i);
-    uint64_t idx = a.large_off[blk] + (i - a.off_large[blk]);
-    uint32_t vid = a.large_vid[idx];
-    uint32_t ch = a.large_chunk[idx];
-    S mu = large_mu[idx];
-    uint64_t rb = row_at<RowT>(a.row, vid);
-    uint64_t re = row_at<RowT>(a.row, vid + 1);
-    uint64_t beg = rb + (uint64_t)ch * kChunk;
-    uint64_t end = min(re, beg + kChunk);
-    for (uint64_t e = beg + threadIdx.x; e < end; e += 64) push_edge<ST, G>(a, e, mu);
+    const uint32_t blk = find_block(sh.off_large, a.blocks, (uint32_t)i);
+    const uint64_t idx = a.large_off[blk] + (i - sh.off_large[blk]);
+    const uint32_t vid = a.large_vid[idx];
+    const uint32_t ch = a.large_chunk[idx];
+    const S mu = large_mu[idx];
+    const uint64_t rb = row_at<RowT>(a.row, vid);
+    const uint64_t re = row_at<RowT>(a.row, vid + 1);
+    const uint64_t beg = rb + (uint64_t)ch * kChunk;
+    const uint64_t end = min(re, beg + kChunk);
+    for (uint64_t e = beg + (threadIdx.x & 63); e < end; e += 64) push_edge<ST, G>(a, e, mu);
   }
 }
 
-// A5: both bins in one launch, the first small_blocks one-wave workgroups on
-// the small bin and the others on the large bin.
+// One workgroup's share of the messages (256 threads).
 template <int ST, int G, typename RowT>
-__global__ __launch_bounds__(64) void k_push(KArgs a, uint32_t small_blocks) {
-  Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl) || ctl->pull) return;
-  if (blockIdx.x < small_blocks) push_small_items<ST, G, RowT>(a, blockIdx.x, small_blocks);
-  else push_large_items<ST, G, RowT>(a, blockIdx.x - small_blocks, gridDim.x - small_blocks);
+__device__ __forceinline__ void push_block(const KArgs& a, PushShared<typename Tr<ST>::S>& sh) {
+  push_prefix(a.blk_small, a.blocks, sh.off_small, sh.wave_sum[0]);
+  push_prefix(a.blk_large, a.blocks, sh.off_large, sh.wave_sum[1]);
+  __syncthreads();
+  const uint32_t wave = threadIdx.x >> 6, nb = 2 * gridDim.x;
+  if (wave < 2) push_small_items<ST, G, RowT>(a, sh, 2 * blockIdx.x + wave, nb);
+  else push_large_items<ST, G, RowT>(a, sh, 2 * blockIdx.x + wave - 2, nb);
+}
+
+template <int ST, int G, typename RowT>
+__global__ __launch_bounds__(256) void k_push(KArgs a) {
+  if (ctl_halted(a.ctl) || a.ctl->pull) return;
+  __shared__ PushShared<typename Tr<ST>::S> sh;
+  push_block<ST, G, RowT>(a, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -1516,6 +1567,7 @@ __global__ __launch_bounds__(256) void k_pull_finish(KArgs a, uint32_t nf, Round
     }
     rr = block_sum256(rr);
     nn = block_sum256(nn);
+    round_counters(a);
     if (tid == 0) {
       ctl->r = rr;
       ctl->pending = nn;

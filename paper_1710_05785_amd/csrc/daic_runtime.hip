@@ -107,7 +107,7 @@ using namespace daic;
 
 namespace daic {
 
-static uint32_t push_grid() { return 256 * 16; }
+static uint32_t push_grid() { return 256 * 8; }  // workgroups of 256
 
 // Per-vertex arrays through the numbering of targets by in-degree octave:
 // dst[r] = src[tinv[r]] (gather) or dst[tinv[r]] = src[r] (scatter).
@@ -216,22 +216,25 @@ struct Impl {
     launch(pr, "claim", s, [&] {
       hipLaunchKernelGGL((k_claim<ST, G, RowT, false>), dim3(a.blocks), dim3(256), 0, s, a);
     });
-    launch(pr, "bin_scan", s, [&] { hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, s, a); });
-    launch(pr, "push_edges", s, [&] {
-      hipLaunchKernelGGL((k_push<ST, G, RowT>), dim3(2 * push_grid()), dim3(64), 0, s, a, push_grid());
-    });
+    const auto push = [&] {
+      hipLaunchKernelGGL((k_push<ST, G, RowT>), dim3(push_grid()), dim3(256), 0, s, a);
+    };
     if (p->pull_ready && p->tile_ready) {  // dense rounds through the tiled in-edges
       const TileArgs t = tile_args(p);
       const uint32_t np = tile_pull_grid(p), nfin = tile_finish_grid(p);
-      launch(pr, "pull_tile", s, [&] {
-        if constexpr (Tr<ST>::sum) {
-          if (t.tw > kNarrowTW) hipLaunchKernelGGL((k_tile_pull<ST, G, false, 1024>), dim3(np), dim3(1024), 0, s, a, t);
-          else hipLaunchKernelGGL((k_tile_pull<ST, G, false, 256>), dim3(np), dim3(256), 0, s, a, t);
-        } else {
-          if (t.tw > kNarrowTW) hipLaunchKernelGGL((k_tile_pull_mm<ST, G, 1024>), dim3(np), dim3(1024), 0, s, a, t);
-          else hipLaunchKernelGGL((k_tile_pull_mm<ST, G, 256>), dim3(np), dim3(256), 0, s, a, t);
-        }
-      });
+      if (t.tw > kNarrowTW) {
+        launch(pr, "push_edges", s, push);
+        launch(pr, "pull_tile", s, [&] {
+          if constexpr (Tr<ST>::sum)
+            hipLaunchKernelGGL((k_tile_pull<ST, G, false, 1024>), dim3(np), dim3(1024), 0, s, a, t);
+          else
+            hipLaunchKernelGGL((k_tile_pull_mm<ST, G, 1024>), dim3(np), dim3(1024), 0, s, a, t);
+        });
+      } else {
+        launch(pr, "propagate", s, [&] {
+          hipLaunchKernelGGL((k_propagate<ST, G, RowT>), dim3(std::max(np, push_grid())), dim3(256), 0, s, a, t);
+        });
+      }
       launch(pr, "settle", s, [&] {
         hipLaunchKernelGGL((k_settle<ST, G>), dim3(std::max(nfin, a.blocks)), dim3(256), 0, s, a, t, nfin);
       });
@@ -240,6 +243,7 @@ struct Impl {
       });
       return;
     }
+    launch(pr, "push_edges", s, push);
     if (p->pull_ready) {
       const uint32_t nf = fused_grid(p);
       launch(pr, "pull_stream", s, [&] {
@@ -277,7 +281,7 @@ struct Impl {
       launch(pr, "claim", s, [&] {
         hipLaunchKernelGGL((k_claim<ST, G, RowT, false>), dim3(a.blocks), dim3(256), 0, s, a);
       });
-      launch(pr, "bin_scan", s, [&] { hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, s, a); });
+      launch(pr, "counters", s, [&] { hipLaunchKernelGGL(k_counters, dim3(1), dim3(256), 0, s, a); });
       hipLaunchKernelGGL(k_fuse_begin, dim3(1), dim3(1), 0, s, a.ctl);
       if (ranked_on(p)) ranked_enter(p, s);
     }
@@ -303,6 +307,7 @@ struct Impl {
     t.n_split = T.n_split;
     t.n_seg = T.n_seg;
     t.tw = 1u << T.tbits;
+    t.pull_grid = tile_pull_grid(p, ranked);
     t.tpart_r = p->tpart_r;
     t.tpart_a = p->tpart_a;
     t.tpart_p = p->tpart_p;
@@ -889,16 +894,15 @@ daic_status daic_problem_create(const daic_graph* g, daic_op op, daic_g gk, doub
   GRAB(large_vid, uint32_t*, g->large_cap * 4);
   GRAB(large_chunk, uint32_t*, g->large_cap * 4);
   GRAB(large_mu, void*, g->large_cap * S);
-  GRAB(blk_small, uint32_t*, nb * 4);
-  GRAB(blk_large, uint32_t*, nb * 4);
+  GRAB(blk_small, uint32_t*, kMaxScanBlocks * 4);
+  GRAB(blk_large, uint32_t*, kMaxScanBlocks * 4);
   GRAB(blk_ties, uint32_t*, nb * 4);
   GRAB(rhist, uint32_t*, kRadixBins * kRadixCopies * 4);
-  GRAB(off_small, uint64_t*, (nb + 1) * 8);
-  GRAB(off_large, uint64_t*, (nb + 1) * 8);
   GRAB(off_ties, uint64_t*, (nb + 1) * 8);
   GRAB(blk_act, uint64_t*, nb * 8);
   GRAB(blk_push, uint64_t*, nb * 8);
   GRAB(blk_push_large, uint64_t*, nb * 8);
+  GRAB(blk_gain, double*, nb * 8);
   GRAB(part_r, double*, nb * 8);
   GRAB(part_n, uint64_t*, nb * 8);
 #undef GRAB
@@ -975,6 +979,8 @@ daic_status daic_problem_create(const daic_graph* g, daic_op op, daic_g gk, doub
     }
     a.alpha_pv = p->alpha_pv;
   }
+  hipLaunchKernelGGL(k_fill<uint32_t>, dim3(8), dim3(256), 0, s, a.blk_small, 0u, (uint64_t)kMaxScanBlocks);
+  hipLaunchKernelGGL(k_fill<uint32_t>, dim3(8), dim3(256), 0, s, a.blk_large, 0u, (uint64_t)kMaxScanBlocks);
   // identity state
   const uint32_t gr = grid_for(n);
   if (st == ST_F64) {
@@ -1387,7 +1393,8 @@ daic_status daic_profile(daic_problem* p, const daic_run_opts* o, uint32_t cap, 
       float ms = 0.f;
       DAIC_HIP(hipEventElapsedTime(&ms, r.a, r.b));
       total_ms += ms;
-      // the two kernels of a round's end are reported by what they did
+      // kernels that serve both directions are reported by what they did
+      if (!std::strcmp(r.name, "propagate")) r.name = c.last_pull ? "pull_tile" : "push_edges";
       if (!std::strcmp(r.name, "settle")) r.name = c.last_pull ? "pull_tile_finish" : "residual";
       if (!std::strcmp(r.name, "total")) r.name = c.last_pull ? "pull_tile_total" : "residual_total";
       // kernels of the other direction return at once: not counted as

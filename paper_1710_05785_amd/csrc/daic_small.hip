@@ -291,10 +291,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(KArgs a, SmallArgs 
       __syncthreads();
       Key ks[4];
       unroll_each<4>([&](auto u) { ks[u] = keys[at[u]]; });
-      uint32_t equal, rem;
-      const Key tau = block_kth<Key, 4>(
-          sel, t.rank, [&](auto u) { return ks[u]; }, [&](auto u) { return tid + u * kSmallThreads < t.S; }, &equal,
-          &rem);
+      const Key tau = block_kth_sampled<Key>(sel, t.rank, t.S, pending, n, ks);
       if (tau != 0) lo = tau;  // no positive sample: every pending vertex
     } else if (t.sched == DAIC_SCHED_TOPK_EXACT) {
       if (pending > t.k) {

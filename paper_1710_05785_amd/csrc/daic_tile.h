@@ -45,6 +45,7 @@ struct TileArgs {
   double* pbuf;               // [n_slots][tw] partial sums of the tiles of split partitions (SlotT<ST>)
   uint64_t m, n_tiles, n_split, n_seg;
   uint32_t tw;                // partition width (a power of two, 1,024..kTileT)
+  uint32_t pull_grid;         // workgroups that walk the tiles
   double* tpart_r;            // per-workgroup partials of k_tile_pull: |new delta|,
   uint64_t* tpart_a;          //   vertex updates,
   uint64_t* tpart_p;          //   messages
@@ -205,13 +206,11 @@ __device__ __forceinline__ void tile_walk(const TileArgs& t, uint32_t e0, uint32
 }
 
 template <int ST, int G, bool FUSED, uint32_t NT>
-__global__ __launch_bounds__(NT) void k_tile_pull(KArgs a, TileArgs t) {
+__device__ __forceinline__ void tile_pull_block(const KArgs& a, const TileArgs& t, double* acc) {
   using S = typename Tr<ST>::S;
   constexpr uint32_t kTileThreads = NT, kTileWaves = TileShape<NT>::waves;
   if constexpr (Tr<ST>::sum) {
-    Ctl* ctl = a.ctl;
-    if (ctl_halted(ctl) || (!FUSED && !ctl->last_pull)) return;
-    __shared__ double acc[TileShape<NT>::cap];
+    const Ctl* ctl = a.ctl;
     const uint32_t tid = threadIdx.x;
     const bool odd = FUSED && ((ctl->rounds - ctl->fuse_base) & 1) != 0;
     const S* mu_in = static_cast<const S*>(odd ? a.mu_pi2 : a.mu_pi);
@@ -225,7 +224,7 @@ __global__ __launch_bounds__(NT) void k_tile_pull(KArgs a, TileArgs t) {
       return x;
     };
     auto add = [&](uint32_t l, double x) { atomicAdd(&acc[l], x); };  // adding 0 leaves a sum as it is
-    for (uint64_t pos = blockIdx.x; pos < t.n_tiles; pos += gridDim.x) {
+    for (uint64_t pos = blockIdx.x; pos < t.n_tiles; pos += t.pull_grid) {
       const uint32_t tile = t.tile_order[pos];
       const uint32_t part = t.tile_part[tile], e0 = t.tile_e[tile], e1 = t.tile_e[tile + 1], slot = t.tile_slot[tile];
       for (uint32_t i = tid; i < t.tw; i += kTileThreads) acc[i] = 0.0;
@@ -243,14 +242,24 @@ __global__ __launch_bounds__(NT) void k_tile_pull(KArgs a, TileArgs t) {
       }
       __syncthreads();
     }
-    r_part = block_sum_waves<kTileWaves>(r_part);
-    act = block_sum_waves<kTileWaves>(act);
-    pushed = block_sum_waves<kTileWaves>(pushed);
+    uint64_t x[2] = {act, pushed};
+    block_sums<kTileWaves>(x, r_part);
+    act = x[0];
+    pushed = x[1];
     if (tid == 0) {
       t.tpart_r[blockIdx.x] = r_part;
       t.tpart_a[blockIdx.x] = act;
       t.tpart_p[blockIdx.x] = pushed;
     }
+  }
+}
+
+template <int ST, int G, bool FUSED, uint32_t NT>
+__global__ __launch_bounds__(NT) void k_tile_pull(KArgs a, TileArgs t) {
+  if constexpr (Tr<ST>::sum) {
+    if (ctl_halted(a.ctl) || (!FUSED && !a.ctl->pull)) return;
+    __shared__ double acc[TileShape<NT>::cap];
+    tile_pull_block<ST, G, FUSED, NT>(a, t, acc);
   }
 }
 
@@ -288,9 +297,10 @@ __device__ __forceinline__ void tile_finish_block(const KArgs& a, const TileArgs
       tile_finish_targets<ST, G, FUSED>(a, mu_out, base, count, tid, 256, [&](uint32_t) { return sum; }, r_part, act,
                                         pushed);
     }
-    r_part = block_sum256(r_part);
-    act = block_sum256(act);
-    pushed = block_sum256(pushed);
+    uint64_t x[2] = {act, pushed};
+    block_sums<4>(x, r_part);
+    act = x[0];
+    pushed = x[1];
     if (tid == 0) {
       t.spart_r[blockIdx.x] = r_part;
       t.spart_a[blockIdx.x] = act;
@@ -315,6 +325,8 @@ __device__ __forceinline__ void tile_totals(const KArgs& a, const TileArgs& t, u
                                             const RoundEnd& e) {
   if constexpr (Tr<ST>::sum || !FUSED) {
     Ctl* ctl = a.ctl;
+    ClaimCounts c;
+    if constexpr (!FUSED) c = claim_counts(a);
     double rr = 0.0;
     uint64_t aa = 0, ps = 0;
     // eight partials per thread at a time, their loads in flight together
@@ -341,9 +353,18 @@ __device__ __forceinline__ void tile_totals(const KArgs& a, const TileArgs& t, u
     };
     add_partials(t.tpart_r, t.tpart_a, t.tpart_p, np);
     add_partials(t.spart_r, t.spart_a, t.spart_p, nf);
-    rr = block_sum256(rr);
-    aa = block_sum256(aa);
-    ps = block_sum256(ps);
+    if constexpr (FUSED) {
+      uint64_t x[2] = {aa, ps};
+      block_sums<4>(x, rr);
+      aa = x[0];
+      ps = x[1];
+    } else {
+      uint64_t x[6] = {aa, c.x[0], c.x[1], c.x[2], c.x[3], c.x[4]};
+      block_sums<4>(x, rr);
+      aa = x[0];
+      if (a.last_upd != nullptr) c.gain = block_sum256(c.gain);  // uniform
+      if (threadIdx.x == 0) store_counts(a, x + 1, c.gain);
+    }
     if (threadIdx.x == 0) {
       ctl->r = Tr<ST>::sum ? rr : (double)aa;  // min/max: rr holds the pending vertices' out-edges
       ctl->rounds += 1;
@@ -457,15 +478,12 @@ __device__ __forceinline__ void tile_mm_finish(const KArgs& a, uint64_t t, typen
 }
 
 template <int ST, int G, uint32_t NT>
-__global__ __launch_bounds__(NT) void k_tile_pull_mm(KArgs a, TileArgs t) {
+__device__ __forceinline__ void tile_pull_block_mm(const KArgs& a, const TileArgs& t, typename TileMM<ST>::L* acc) {
   constexpr uint32_t kTileThreads = NT, kTileWaves = TileShape<NT>::waves;
   if constexpr (!Tr<ST>::sum) {
     using S = typename Tr<ST>::S;
     using M = TileMM<ST>;
     using L = typename M::L;
-    Ctl* ctl = a.ctl;
-    if (ctl_halted(ctl) || !ctl->last_pull) return;
-    __shared__ L acc[TileShape<NT>::cap];
     const uint32_t tid = threadIdx.x;
     const S* mu_in = static_cast<const S*>(a.mu_pi);
     const S* v = static_cast<const S*>(a.v);
@@ -476,7 +494,7 @@ __global__ __launch_bounds__(NT) void k_tile_pull_mm(KArgs a, TileArgs t) {
     auto add = [&](uint32_t l, L x) {
       if (x != M::ident) M::combine(&acc[l], x);
     };
-    for (uint64_t pos = blockIdx.x; pos < t.n_tiles; pos += gridDim.x) {
+    for (uint64_t pos = blockIdx.x; pos < t.n_tiles; pos += t.pull_grid) {
       const uint32_t tile = t.tile_order[pos];
       const uint32_t part = t.tile_part[tile], e0 = t.tile_e[tile], e1 = t.tile_e[tile + 1], slot = t.tile_slot[tile];
       for (uint32_t i = tid; i < t.tw; i += kTileThreads) acc[i] = M::ident;
@@ -494,13 +512,23 @@ __global__ __launch_bounds__(NT) void k_tile_pull_mm(KArgs a, TileArgs t) {
       }
       __syncthreads();
     }
-    r_part = block_sum_waves<kTileWaves>(r_part);
-    act = block_sum_waves<kTileWaves>(act);
+    uint64_t x[1] = {act};
+    block_sums<kTileWaves>(x, r_part);
+    act = x[0];
     if (tid == 0) {
       t.tpart_r[blockIdx.x] = r_part;
       t.tpart_a[blockIdx.x] = act;
       t.tpart_p[blockIdx.x] = 0;
     }
+  }
+}
+
+template <int ST, int G, uint32_t NT>
+__global__ __launch_bounds__(NT) void k_tile_pull_mm(KArgs a, TileArgs t) {
+  if constexpr (!Tr<ST>::sum) {
+    if (ctl_halted(a.ctl) || !a.ctl->pull) return;
+    __shared__ typename TileMM<ST>::L acc[TileShape<NT>::cap];
+    tile_pull_block_mm<ST, G, NT>(a, t, acc);
   }
 }
 
@@ -539,13 +567,37 @@ __device__ __forceinline__ void tile_finish_block_mm(const KArgs& a, const TileA
       }
       tile_mm_finish<ST>(a, base + tid, x, v[base + tid], dv[base + tid], r_part, act);
     }
-    r_part = block_sum256(r_part);
-    act = block_sum256(act);
+    uint64_t x[1] = {act};
+    block_sums<4>(x, r_part);
+    act = x[0];
     if (tid == 0) {
       t.spart_r[blockIdx.x] = r_part;
       t.spart_a[blockIdx.x] = act;
       t.spart_p[blockIdx.x] = 0;
     }
+  }
+}
+
+// A round's messages in either direction, where both forms run workgroups of
+// 256 threads: the first np workgroups walk the tiles in a dense round, all of
+// them push in a sparse one (the kernel of the other direction, returning at
+// once, cost 4.5 us a round).
+template <int ST, int G, typename RowT>
+__global__ __launch_bounds__(256) void k_propagate(KArgs a, TileArgs t) {
+  using S = typename Tr<ST>::S;
+  const Ctl* ctl = a.ctl;
+  if (ctl_halted(ctl)) return;
+  union Shared {
+    __device__ Shared() {}
+    PushShared<S> push;
+    double acc[TileShape<256>::cap];  // FP64 sums, or minima and maxima of 4 or 8 bytes
+  };
+  __shared__ Shared sh;
+  if (!ctl->pull) {
+    push_block<ST, G, RowT>(a, sh.push);
+  } else if (blockIdx.x < t.pull_grid) {
+    if constexpr (Tr<ST>::sum) tile_pull_block<ST, G, false, 256>(a, t, sh.acc);
+    else tile_pull_block_mm<ST, G, 256>(a, t, reinterpret_cast<typename TileMM<ST>::L*>(sh.acc));
   }
 }
 
