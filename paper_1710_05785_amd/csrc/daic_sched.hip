@@ -631,30 +631,31 @@ struct MlpRegs {
   float b3;
 };
 
-__device__ __forceinline__ uint32_t mlp_unit(int s, uint32_t q, int j) {
-  return 32 * s + (j < 4 ? 4 * q + j : 16 + 4 * q + (j - 4));
-}
-
 __device__ __forceinline__ void mlp_regs(const MlpDev& m, MlpRegs& R) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t q = lane >> 4, r = lane & 15;
+  // four consecutive BF16 values (8-byte aligned: rows of 4 and of 64) or
+  // biases per load
+  auto four = [](const uint16_t* p) { return *reinterpret_cast<const bf16x4*>(p); };
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
+    const bf16x4 none = {0, 0, 0, 0};
+    R.w1[t] = q == 0 ? four(m.W1b + (16 * t + r) * 4) : none;
+    R.b1[t] = *reinterpret_cast<const f32x4*>(m.b1 + 16 * t + 4 * q);
+    R.b2[t] = *reinterpret_cast<const f32x4*>(m.b2 + 16 * t + 4 * q);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      R.w1[t][i] = q == 0 ? (short)m.W1b[(16 * t + r) * 4 + i] : (short)0;
-      R.b1[t][i] = m.b1[16 * t + 4 * q + i];
-      R.b2[t][i] = m.b2[16 * t + 4 * q + i];
+    for (int st = 0; st < 2; ++st) {
+      const uint16_t* w = m.W2b + (16 * t + r) * kH + 32 * st + 4 * q;
+      R.w2[t][st] = __builtin_shufflevector(four(w), four(w + 16), 0, 1, 2, 3, 4, 5, 6, 7);
     }
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) R.w2[t][st][j] = (short)m.W2b[(16 * t + r) * kH + mlp_unit(st, q, j)];
   }
 #pragma unroll
-  for (int st = 0; st < 2; ++st)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) R.w3[st][j] = r == 0 ? (short)m.W3b[mlp_unit(st, q, j)] : (short)0;
+  for (int st = 0; st < 2; ++st) {
+    const uint16_t* w = m.W3b + 32 * st + 4 * q;
+    const i16x8v x = __builtin_shufflevector(four(w), four(w + 16), 0, 1, 2, 3, 4, 5, 6, 7);
+    const i16x8v none = {0, 0, 0, 0, 0, 0, 0, 0};
+    R.w3[st] = r == 0 ? x : none;
+  }
   R.b3 = m.b3[0];
 }
 
@@ -803,11 +804,15 @@ __global__ void k_trace_window(KArgs a, TraceDev td, uint64_t first, uint64_t la
   }
 }
 
+constexpr uint64_t kScoreBlocks = 1024;  // 256 CUs x 4 workgroups of k_score
+
 template <int ST, typename RowT>
 struct LearnedImpl {
   static void score(daic_problem* p, const daic_sched_model* m, const FeatNorm& fn, hipStream_t s) {
-    const uint64_t tiles = (p->a.n + 15) / 16;
-    const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((tiles + 3) / 4, 8192));
+    // as many waves as are resident, each with several groups of 64 vertices:
+    // a wave loads the whole network first (with 8,192 workgroups half the
+    // waves of a million vertices had nothing to score after it)
+    const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((p->a.n + 255) / 256, kScoreBlocks));
     hipLaunchKernelGGL((k_score<ST, RowT>), dim3(blocks), dim3(256), 0, s, p->a, m->dev(), fn, p->indeg,
                        p->last_upd, p->score);
   }
