@@ -302,7 +302,19 @@ static void tile_shape(const daic_graph* g, uint32_t* lb_out, uint64_t* max_edge
   // (DAIC_TILE_BITS overrides it)
   uint32_t lb = tile_default_bits(n);
   if (const char* e = std::getenv("DAIC_TILE_BITS")) lb = (uint32_t)std::max(8ul, std::min(14ul, std::strtoul(e, nullptr, 10)));
-  uint64_t max_edges = std::max<uint64_t>(tile_default_edges(n, m, lb), m / ((uint64_t)std::max(cus, 1) * tile_wgs_per_cu(lb)));
+  // partitions of 2^10 and 2^11 targets, several workgroups to a CU: at least
+  // one partition's average rather than the default's two. Where a few
+  // hundred to two thousand tiles cover the graph, the last workgroups to end
+  // are those with two averages, and finishing the partitions split at one
+  // costs less than they did (us per round, two -> one: PageRank on RMAT-19
+  // 45.5 -> 43.8, RMAT-20 58.3 -> 53.6, RMAT-21 89.6 -> 81.0 and in f64
+  // 104.1 -> 103.1, components on 262,144 vertices 32.8 -> 30.4, SSSP on
+  // RMAT-20 102.6 -> 92.3; 0.75 of the average and 1.25 were slower). From
+  // 2^12 targets on a split partition's finish is dearer: RMAT-22 in f64
+  // took 193 us at two averages, 212 at one
+  const uint64_t n_part = std::max<uint64_t>(1, (n + (1ull << lb) - 1) >> lb);
+  const uint64_t least = lb <= 11 ? std::max<uint64_t>(16384, std::min<uint64_t>(kTileE, m / n_part)) : tile_default_edges(n, m, lb);
+  uint64_t max_edges = std::max<uint64_t>(least, m / ((uint64_t)std::max(cus, 1) * tile_wgs_per_cu(lb)));
   if (const char* e = std::getenv("DAIC_TILE_EDGES")) max_edges = std::strtoull(e, nullptr, 10);
   *lb_out = lb;
   *max_edges_out = max_edges;
