@@ -270,7 +270,7 @@ daic_status daic_select_frontier(daic_problem* p, const daic_run_opts* opts, uin
  * taken). Inputs are only read. It allocates nothing and does not
  * synchronize: kernels are enqueued on opts->hip_stream (NULL = default
  * stream) and the call returns. Its scratch (control block, radix
- * histograms, sampled keys, per-block partials: under 160 KiB, the same for every
+ * histograms, per-block partials: under 160 KiB, the same for every
  * n up to the maximum n < 2^32 - 1) is one fixed array per device that every
  * call on that device shares and overwrites, so calls that overlap on one
  * device (other streams, other threads) race and must be serialized by the

@@ -37,6 +37,7 @@ constexpr uint32_t kInfU32 = 0xFFFFFFFFu;
 // ---- device control block -----------------------------------------------------
 // One per problem, in device memory. Written by the round kernels, read by the
 // host once per check.
+constexpr int kMaxRadixPasses = 6;  // 64-bit keys, 11 bits a pass
 struct Ctl {
   double r;              // residual of the current state
   double eps;            // stop threshold for sum problems
@@ -57,8 +58,8 @@ struct Ctl {
   uint32_t sel_mode;     // 0 all pending; 1 key >= tau; 2 key > tau, or == tau within ties
   uint64_t tau;          // threshold key of this round
   uint64_t ties_left;    // keys equal to tau to take (sel_mode 2)
-  uint64_t k_rem;        // radix select: rank still to place
-  uint64_t radix_prefix; // radix select: key bits fixed so far
+  uint64_t k_rem[kMaxRadixPasses];         // radix select: rank to place in pass i
+  uint64_t radix_prefix[kMaxRadixPasses];  // radix select: key bits fixed before pass i
   uint32_t radix_skip;   // radix select: nothing to do (all pending fit)
   uint32_t pull;         // the next round runs as a pull over in-edges (dense round)
   uint32_t last_pull;    // the round just run was a dense round

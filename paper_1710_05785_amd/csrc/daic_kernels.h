@@ -1,7 +1,7 @@
 // Device code of one DAIC round on gfx950 (64-lane wavefronts).
 //
 // A round (Eq. async of the paper applied to a selected set, Sec. 3.2/3.4):
-//   A2 k_sample, or k_radix_pass + k_radix_pick per digit and k_ties
+//   A2 k_sample, or k_radix_pass per digit and k_ties
 //                           : threshold of the priority keys (sampled or exact)
 //   A3+A4 k_claim           : select, claim dv_j, fold v_j (+)= delta, compute
 //                             the message base mu_j, compact into degree bins
@@ -68,7 +68,7 @@ struct KArgs {
   uint64_t* blk_push_large;
   double* blk_gain;         // learned runs: per-block priority realized by the selected vertices
   uint32_t* blk_ties;       // exact top-k: keys equal to tau per block
-  uint32_t* rhist;          // exact top-k: radix histogram (kRadixCopies x kRadixBins counters)
+  uint32_t* rhist;          // exact top-k: radix histograms (kRadixSets x kRadixCopies x kRadixBins counters)
   uint64_t* off_ties;       // exclusive prefix of blk_ties
   double* part_r;           // residual partials per block
   uint64_t* part_n;         // pending-count partials per block
@@ -381,8 +381,8 @@ __device__ __forceinline__ void topk_begin(Ctl* ctl, uint64_t pending, uint64_t 
   const bool all = pending <= k;
   ctl->sel_mode = all ? 0u : 2u;
   ctl->radix_skip = all ? 1u : 0u;
-  ctl->k_rem = k;
-  ctl->radix_prefix = 0;
+  ctl->k_rem[0] = k;
+  ctl->radix_prefix[0] = 0;
 }
 
 // Learned scheduling, before a round: remember the residual and decide
@@ -787,7 +787,12 @@ constexpr int kRadixBits = 11;
 constexpr uint32_t kRadixBins = 1u << kRadixBits;
 // copies of the global histogram: workgroup b adds into copy b mod
 // kRadixCopies, so each counter takes a fraction of the atomics
-constexpr uint32_t kRadixCopies = 8;
+constexpr uint32_t kRadixCopies = 2;
+// Histograms in rotation: pass i adds into set i mod 3, reads that of pass
+// i - 1 and clears the one that pass i - 2 left, so a selection finds set 0
+// clear, and the others clear by the time it adds into them.
+constexpr uint32_t kRadixSets = 3;
+constexpr uint32_t kRadixWords = kRadixSets * kRadixCopies * kRadixBins;
 
 template <typename Key>
 constexpr int radix_passes() {
@@ -803,90 +808,44 @@ __device__ __forceinline__ void radix_digit(int key_bits, int pass, int& shift, 
 }
 
 // One block of 256 threads: clears the histograms and starts the select (the
-// rounds of a run start it when the round before ends, and every pick leaves
-// the histograms clear).
+// rounds of a run start it when the round before ends, and the passes leave
+// the histograms as the next selection needs them).
 static __global__ __launch_bounds__(256) void k_topk_init(Ctl* ctl, uint32_t* rhist, uint64_t k) {
-  for (uint32_t i = threadIdx.x; i < kRadixBins * kRadixCopies; i += 256) rhist[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kRadixWords; i += 256) rhist[i] = 0;
   if (threadIdx.x != 0 || ctl_halted(ctl)) return;
   topk_begin(ctl, ctl->pending, k);
 }
 
-// One pass: every workgroup counts the digits of the keys that match the
-// prefix in LDS and adds its counts into its copy of the global histogram;
-// k_radix_pick then picks the digit.
-template <int ST>
-__global__ __launch_bounds__(256) void k_radix_pass(KArgs a, int pass) {
-  if (a.score != nullptr && !a.ctl->use_score) a.score = nullptr;  // an exact round of a learned run
-  using S = typename Tr<ST>::S;
-  using Key = typename Tr<ST>::Key;
-  Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl) || ctl->radix_skip) return;
-  constexpr int kBits = sizeof(Key) * 8;
+// A block of 1,024 threads: the digit of pass `pass` that holds the k_rem-th
+// largest key, from the sum of the histogram's copies (bins scanned from the
+// top, two per thread, so that every load is in flight at once). Every
+// workgroup of the kernel after the pass finds it for itself: a kernel of one
+// workgroup between two passes cost 5.7 us of each pass's 10.5, this costs
+// under 2 and runs beside the loads of the workgroup's first keys.
+struct RadixPick {
+  uint64_t prefix;  // key bits fixed through this pass
+  uint64_t rem;     // rank to place among the keys that match them
+  uint32_t eq;      // keys that match them
+  uint32_t found;   // 0: fewer keys than k (not reached: pending > k)
+};
+template <typename Key>
+__device__ __forceinline__ RadixPick radix_pick(const Ctl* ctl, const uint32_t* rhist, int pass) {
   int shift, width;
-  radix_digit(kBits, pass, shift, width);
-  const Key hi_mask = pass == 0 ? (Key)0 : (Key)(~(Key)0 << (shift + width));
-  const Key prefix = (Key)ctl->radix_prefix;
-  const uint32_t nbins = 1u << width, dmask = nbins - 1;
-  const uint32_t tid = threadIdx.x;
-  __shared__ uint32_t h[kRadixBins];
-  for (uint32_t i = tid; i < nbins; i += 256) h[i] = 0;
-  __syncthreads();
-  const S* v = static_cast<const S*>(a.v);
-  const S* dv = static_cast<const S*>(a.dv);
-  constexpr int U = 8;
-  const uint64_t stride = (uint64_t)gridDim.x * 256 * U;
-  // U keys per step, their loads in flight together
-  for (uint64_t j0 = (uint64_t)blockIdx.x * 256 * U + tid; j0 < a.n; j0 += stride) {
-    S vv[U], dd[U];
-    float sc[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint64_t j = min(j0 + 256 * u, a.n - 1);
-      vv[u] = v[j];
-      dd[u] = dv[j];
-      sc[u] = a.score != nullptr ? a.score[j] : 1.f;
-    }
-    Key k[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) k[u] = sel_key_loaded<ST>(a, vv[u], dd[u], sc[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (j0 + 256 * u < a.n && k[u] != 0 && (k[u] & hi_mask) == prefix)
-        atomicAdd(&h[(uint32_t)(k[u] >> shift) & dmask], 1u);
-  }
-  __syncthreads();
-  uint32_t* hist = a.rhist + (blockIdx.x % kRadixCopies) * kRadixBins;
-  for (uint32_t i = tid; i < nbins; i += 256) {
-    const uint32_t c = h[i];
-    if (c) atomicAdd(&hist[i], c);
-  }
-}
-
-// After a pass (one block of 1,024 threads): the digit that holds the
-// k_rem-th largest key, from the sum of the histogram copies (bins scanned
-// from the top, two per thread, so that every load is in flight at once: a
-// block of 256 with eight bins each took 9 us); it is fixed in the prefix and
-// the copies are cleared for the next pass.
-template <int ST>
-__global__ __launch_bounds__(1024) void k_radix_pick(KArgs a, int pass) {
-  using Key = typename Tr<ST>::Key;
-  Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl) || ctl->radix_skip) return;
-  constexpr int kBits = sizeof(Key) * 8;
-  int shift, width;
-  radix_digit(kBits, pass, shift, width);
+  radix_digit(sizeof(Key) * 8, pass, shift, width);
   const uint32_t nbins = 1u << width;
   const uint32_t tid = threadIdx.x, wave = tid >> 6;
-  __shared__ uint32_t s_found, s_wave[16];
+  const uint32_t* hist = rhist + (uint32_t)(pass % (int)kRadixSets) * (kRadixCopies * kRadixBins);
+  __shared__ RadixPick s_pick;
+  __shared__ uint32_t s_wave[16];
   // bins from the top: thread t holds bins nbins - 1 - 2t - q, q = 0, 1
   uint32_t x[2][kRadixCopies];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const uint32_t r = tid * 2 + q;
 #pragma unroll
-    for (uint32_t cp = 0; cp < kRadixCopies; ++cp)
-      x[q][cp] = r < nbins ? a.rhist[cp * kRadixBins + nbins - 1 - r] : 0u;
+    for (uint32_t cp = 0; cp < kRadixCopies; ++cp) x[q][cp] = r < nbins ? hist[cp * kRadixBins + nbins - 1 - r] : 0u;
   }
+  const uint64_t k = ctl->k_rem[pass];
   uint32_t c[2] = {0, 0};
 #pragma unroll
   for (int q = 0; q < 2; ++q)
@@ -895,97 +854,192 @@ __global__ __launch_bounds__(1024) void k_radix_pick(KArgs a, int pass) {
   const uint32_t mine = c[0] + c[1];
   const uint32_t incl = wave_incl_scan(mine);
   if (lane_id() == 63) s_wave[wave] = incl;
-  if (tid == 0) s_found = 0;
+  if (tid == 0) s_pick.found = 0;
   __syncthreads();
   uint64_t above = incl - mine;  // keys in the bins above this thread's
 #pragma unroll
   for (uint32_t w = 0; w < 16; ++w) above += w < wave ? s_wave[w] : 0u;
-  const uint64_t k = ctl->k_rem;
   if (above < k && k <= above + mine) {  // one thread
     const int q = above + c[0] >= k ? 0 : 1;
     const uint64_t d = nbins - 1 - (tid * 2 + q);
-    const uint64_t rem = k - above - (q ? c[0] : 0u);
-    ctl->k_rem = rem;
-    ctl->radix_prefix |= d << shift;
-    if (shift == 0) {
-      ctl->tau = ctl->radix_prefix;
-      ctl->ties_left = rem;
-      ctl->sel_mode = c[q] == rem ? 1u : 2u;  // all equal keys fit: no tie ranks
-    }
-    s_found = 1;
+    s_pick.prefix = ctl->radix_prefix[pass] | d << shift;
+    s_pick.rem = k - above - (q ? c[0] : 0u);
+    s_pick.eq = c[q];
+    s_pick.found = 1;
   }
   __syncthreads();
-  if (tid == 0 && !s_found) {  // fewer keys than k (not reached: pending > k)
-    ctl->sel_mode = 0;
-    ctl->radix_skip = 1;
-  }
-#pragma unroll
-  for (int q = 0; q < 2; ++q)
-    if (tid * 2 + q < nbins)
-#pragma unroll
-      for (uint32_t cp = 0; cp < kRadixCopies; ++cp) a.rhist[cp * kRadixBins + tid * 2 + q] = 0;
+  return s_pick;
 }
 
-// Keys equal to the threshold, where only some of them are taken: the count
-// of every block and, by the block that ends last, their exclusive prefix.
+// One pass: every workgroup picks the digit of the pass before, counts the
+// digits of the keys that match the prefix in LDS and adds its counts into
+// its copy of the pass's histogram. 256 workgroups of 1,024 threads, one per
+// CU, where 1,024 of 256 would each pick and each flush their counts. The
+// selection of a round took 40.7 us on RMAT-20 and 52.8 us on RMAT-22 with
+// picking kernels between the passes, and takes 25.1 and 36.3 us
 template <int ST>
-__global__ __launch_bounds__(256) void k_ties(KArgs a) {
+__global__ __launch_bounds__(1024) void k_radix_pass(KArgs a, int pass) {
   if (a.score != nullptr && !a.ctl->use_score) a.score = nullptr;  // an exact round of a learned run
   using S = typename Tr<ST>::S;
   using Key = typename Tr<ST>::Key;
+  constexpr int kPasses = radix_passes<Key>();
+  static_assert(kPasses % kRadixSets != 1 && kPasses <= kMaxRadixPasses);  // the last pass leaves set 0 clear
   Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl) || ctl->sel_mode != 2) return;
-  const Key tau = (Key)ctl->tau;
-  const uint64_t lo = (uint64_t)blockIdx.x * a.per_block;
-  const uint64_t hi = min(a.n, lo + a.per_block);
+  if (ctl_halted(ctl) || ctl->radix_skip) return;
+  int shift, width;
+  radix_digit(sizeof(Key) * 8, pass, shift, width);
+  const uint32_t nbins = 1u << width, dmask = nbins - 1;
+  const uint32_t tid = threadIdx.x;
+  __shared__ uint32_t h[kRadixBins];
   const S* v = static_cast<const S*>(a.v);
   const S* dv = static_cast<const S*>(a.dv);
-  uint32_t cnt = 0;
-  // four vertices per step, their loads in flight together
-  for (uint64_t j0 = lo + threadIdx.x; j0 < hi; j0 += 1024) {
-    S vv[4], dd[4];
-    float sc[4];
+  constexpr int U = 4;
+  const uint64_t stride = (uint64_t)gridDim.x * 1024 * U;
+  // U keys per step, their loads in flight together
+  S vv[U], dd[U];
+  float sc[U];
+  auto load = [&](uint64_t j0) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint64_t j = min(j0 + 256 * u, hi - 1);
+    for (int u = 0; u < U; ++u) {
+      const uint64_t j = min(j0 + 1024 * u, a.n - 1);
       vv[u] = v[j];
       dd[u] = dv[j];
       sc[u] = a.score != nullptr ? a.score[j] : 1.f;
     }
+  };
+  uint64_t j0 = (uint64_t)blockIdx.x * 1024 * U + tid;
+  load(j0);
+  for (uint32_t i = tid; i < nbins; i += 1024) h[i] = 0;
+  uint32_t* clear = a.rhist + (uint32_t)((pass + 1) % (int)kRadixSets) * (kRadixCopies * kRadixBins);
+  for (uint32_t i = blockIdx.x * 1024 + tid; i < kRadixCopies * kRadixBins; i += gridDim.x * 1024) clear[i] = 0;
+  Key hi_mask = 0, prefix = 0;
+  if (pass > 0) {
+    const RadixPick pk = radix_pick<Key>(ctl, a.rhist, pass - 1);
+    if (!pk.found) {
+      if (blockIdx.x == 0 && tid == 0) {
+        ctl->sel_mode = 0;
+        ctl->radix_skip = 1;
+      }
+      return;
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+      ctl->radix_prefix[pass] = pk.prefix;
+      ctl->k_rem[pass] = pk.rem;
+    }
+    prefix = (Key)pk.prefix;
+    hi_mask = (Key)(~(Key)0 << (shift + width));
+  } else {
+    __syncthreads();
+  }
+  while (j0 < a.n) {
+    Key k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) k[u] = sel_key_loaded<ST>(a, vv[u], dd[u], sc[u]);
+    const uint64_t j = j0;
+    j0 += stride;
+    if (j0 < a.n) load(j0);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (j + 1024 * u < a.n && k[u] != 0 && (k[u] & hi_mask) == prefix)
+        atomicAdd(&h[(uint32_t)(k[u] >> shift) & dmask], 1u);
+  }
+  __syncthreads();
+  uint32_t* hist = a.rhist + ((uint32_t)(pass % (int)kRadixSets) * kRadixCopies + blockIdx.x % kRadixCopies) * kRadixBins;
+  for (uint32_t i = tid; i < nbins; i += 1024) {
+    const uint32_t c = h[i];
+    if (c) atomicAdd(&hist[i], c);
+  }
+}
+
+// After the passes: the last digit, which completes the threshold, and, where
+// only some of the keys equal to it are taken, their count in every block of
+// vertices and, by the workgroup that ends last, the exclusive prefix. A
+// workgroup of 1,024 threads takes four blocks of vertices, one per 256
+// threads.
+template <int ST>
+__global__ __launch_bounds__(1024) void k_ties(KArgs a) {
+  if (a.score != nullptr && !a.ctl->use_score) a.score = nullptr;  // an exact round of a learned run
+  using S = typename Tr<ST>::S;
+  using Key = typename Tr<ST>::Key;
+  constexpr int kPasses = radix_passes<Key>();
+  Ctl* ctl = a.ctl;
+  if (ctl_halted(ctl) || ctl->radix_skip) return;
+  const uint32_t tid = threadIdx.x, quarter = tid >> 8, qt = tid & 255, wave = tid >> 6;
+  const uint32_t blk = blockIdx.x * 4 + quarter;
+  const uint64_t lo = min(a.n, (uint64_t)blk * a.per_block);  // (no vertices from block a.blocks on)
+  const uint64_t hi = min(a.n, lo + a.per_block);
+  const S* v = static_cast<const S*>(a.v);
+  const S* dv = static_cast<const S*>(a.dv);
+  // four vertices per step, their loads in flight together
+  S vv[4], dd[4];
+  float sc[4];
+  auto load = [&](uint64_t j0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint64_t j = min(j0 + 256 * u, a.n - 1);
+      vv[u] = v[j];
+      dd[u] = dv[j];
+      sc[u] = a.score != nullptr ? a.score[j] : 1.f;
+    }
+  };
+  uint64_t j0 = lo + qt;
+  load(j0);
+  uint32_t* clear = a.rhist + (uint32_t)((kPasses + 1) % (int)kRadixSets) * (kRadixCopies * kRadixBins);
+  for (uint32_t i = blockIdx.x * 1024 + tid; i < kRadixCopies * kRadixBins; i += gridDim.x * 1024) clear[i] = 0;
+  const RadixPick pk = radix_pick<Key>(ctl, a.rhist, kPasses - 1);
+  const bool ties = pk.found && pk.eq != pk.rem;  // else all equal keys fit: no tie ranks
+  if (blockIdx.x == 0 && tid == 0) {
+    ctl->sel_mode = !pk.found ? 0u : ties ? 2u : 1u;
+    ctl->tau = pk.prefix;
+    ctl->ties_left = pk.rem;
+  }
+  if (!ties) return;
+  const Key tau = (Key)pk.prefix;
+  uint32_t cnt = 0;
+  while (j0 < hi) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       cnt += (j0 + 256 * u < hi && sel_key_loaded<ST>(a, vv[u], dd[u], sc[u]) == tau) ? 1u : 0u;
+    j0 += 1024;
+    if (j0 < hi) load(j0);
   }
-  cnt = block_sum256(cnt);
-  __shared__ uint32_t s_last, s_wave[4];
-  if (threadIdx.x == 0) {
-    __hip_atomic_store(&a.blk_ties[blockIdx.x], cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  cnt = wave_sum(cnt);
+  __shared__ uint32_t s_last, s_wave[16];
+  if (lane_id() == 0) s_wave[wave] = cnt;
+  __syncthreads();
+  if (tid < 4 && blockIdx.x * 4 + tid < a.blocks) {
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < 4; ++w) c += s_wave[tid * 4 + w];
+    __hip_atomic_store(&a.blk_ties[blockIdx.x * 4 + tid], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __threadfence();
-    s_last = atomicAdd(&ctl->ticket, 1u) == gridDim.x - 1;
   }
+  // (thread 0 follows the three other stores of its wave)
+  if (tid == 0) s_last = atomicAdd(&ctl->ticket, 1u) == gridDim.x - 1;
   __syncthreads();
   if (!s_last) return;
   __threadfence();
-  constexpr uint32_t PER = kMaxScanBlocks / 256;  // blocks per thread, consecutive
+  constexpr uint32_t PER = kMaxScanBlocks / 1024;  // blocks per thread, consecutive
   uint32_t x[PER], sum = 0;
 #pragma unroll
   for (uint32_t u = 0; u < PER; ++u) {
-    const uint32_t i = threadIdx.x * PER + u;
-    x[u] = i < gridDim.x ? __hip_atomic_load(&a.blk_ties[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const uint32_t i = tid * PER + u;
+    x[u] = i < a.blocks ? __hip_atomic_load(&a.blk_ties[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     sum += x[u];
   }
-  const uint32_t incl = wave_incl_scan(sum), wave = threadIdx.x >> 6;
+  const uint32_t incl = wave_incl_scan(sum);
   if (lane_id() == 63) s_wave[wave] = incl;
   __syncthreads();
   uint64_t at = incl - sum;
-  for (uint32_t w = 0; w < wave; ++w) at += s_wave[w];
+#pragma unroll
+  for (uint32_t w = 0; w < 16; ++w) at += w < wave ? s_wave[w] : 0u;
 #pragma unroll
   for (uint32_t u = 0; u < PER; ++u) {
-    const uint32_t i = threadIdx.x * PER + u;
-    if (i < gridDim.x) a.off_ties[i] = at;
+    const uint32_t i = tid * PER + u;
+    if (i < a.blocks) a.off_ties[i] = at;
     at += x[u];
   }
-  if (threadIdx.x == 0) ctl->ticket = 0;
+  if (tid == 0) ctl->ticket = 0;
 }
 
 // Progress metric sum_j v_j of the current state (FP64; min problems skip

@@ -24,7 +24,7 @@ constexpr size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign;
 // kMaxScanBlocks blocks whatever n is, so the size does not depend on n.
 constexpr size_t kOffCtl = 0;
 constexpr size_t kOffHist = align_up(kOffCtl + sizeof(Ctl));
-constexpr size_t kOffTies = align_up(kOffHist + (size_t)kRadixBins * kRadixCopies * 4);
+constexpr size_t kOffTies = align_up(kOffHist + (size_t)kRadixWords * 4);
 constexpr size_t kOffTieOff = align_up(kOffTies + (size_t)kMaxScanBlocks * 4);
 constexpr size_t kOffPartR = align_up(kOffTieOff + ((size_t)kMaxScanBlocks + 1) * 8);
 constexpr size_t kOffPartN = align_up(kOffPartR + (size_t)kMaxScanBlocks * 8);
@@ -91,13 +91,11 @@ void enqueue_select(const KArgs& a, const daic_run_opts* o, uint64_t round, doub
   } else {
     uint64_t k = (uint64_t)std::ceil(o->priority_fraction * (double)n);
     if (k < 1) k = 1;
-    const uint32_t hgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(1024, (n + 1023) / 1024));
+    const uint32_t hgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(256, (n + 4095) / 4096));
     hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(256), 0, s, a.ctl, a.rhist, k);
-    for (int pass = 0; pass < radix_passes<Key>(); ++pass) {
-      hipLaunchKernelGGL(k_radix_pass<ST>, dim3(hgrid), dim3(256), 0, s, a, pass);
-      hipLaunchKernelGGL(k_radix_pick<ST>, dim3(1), dim3(1024), 0, s, a, pass);
-    }
-    hipLaunchKernelGGL(k_ties<ST>, dim3(a.blocks), dim3(256), 0, s, a);
+    for (int pass = 0; pass < radix_passes<Key>(); ++pass)
+      hipLaunchKernelGGL(k_radix_pass<ST>, dim3(hgrid), dim3(1024), 0, s, a, pass);
+    hipLaunchKernelGGL(k_ties<ST>, dim3((a.blocks + 3) / 4), dim3(1024), 0, s, a);
   }
   // row offsets are not read by the selection-only claim
   hipLaunchKernelGGL((k_claim<ST, G, uint32_t, true>), dim3(a.blocks), dim3(256), 0, s, a);

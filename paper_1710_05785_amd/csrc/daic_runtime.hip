@@ -194,15 +194,13 @@ struct Impl {
       uint64_t k = (uint64_t)std::ceil(o->priority_fraction * (double)n);
       if (k < 1) k = 1;
       const int passes = radix_passes<Key>();
-      uint32_t hgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(1024, (n + 1023) / 1024));
+      const uint32_t hgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(256, (n + 4095) / 4096));
       launch(pr, "topk_radix", s, [&] {
         // a run's selections are started by the end of the round before (RoundEnd)
         if (begin) hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(256), 0, s, a.ctl, a.rhist, k);
-        for (int pass = 0; pass < passes; ++pass) {
-          hipLaunchKernelGGL(k_radix_pass<ST>, dim3(hgrid), dim3(256), 0, s, a, pass);
-          hipLaunchKernelGGL(k_radix_pick<ST>, dim3(1), dim3(1024), 0, s, a, pass);
-        }
-        hipLaunchKernelGGL(k_ties<ST>, dim3(a.blocks), dim3(256), 0, s, a);
+        for (int pass = 0; pass < passes; ++pass)
+          hipLaunchKernelGGL(k_radix_pass<ST>, dim3(hgrid), dim3(1024), 0, s, a, pass);
+        hipLaunchKernelGGL(k_ties<ST>, dim3((a.blocks + 3) / 4), dim3(1024), 0, s, a);
       });
     }
   }
@@ -520,8 +518,8 @@ daic_status check_opts(const daic_problem* p, const daic_run_opts* o) {
 
 void clear_radix(daic_problem* p, hipStream_t s) {
   if (p->end.topk)
-    hipLaunchKernelGGL(k_fill<uint32_t>, dim3(grid_for(kRadixBins * kRadixCopies)), dim3(256), 0, s, p->a.rhist, 0u,
-                       (uint64_t)(kRadixBins * kRadixCopies));
+    hipLaunchKernelGGL(k_fill<uint32_t>, dim3(grid_for(kRadixWords)), dim3(256), 0, s, p->a.rhist, 0u,
+                       (uint64_t)kRadixWords);
 }
 
 // Dense rounds (pull over in-edges) for sum problems: builds the in-edge form
@@ -899,13 +897,13 @@ daic_status daic_problem_create(const daic_graph* g, daic_op op, daic_g gk, doub
   {
     char* at = nullptr;
     const size_t nb8 = ((size_t)nb + 1) * 8;
-    rc = grab(&ptr, kMaxScanBlocks * 8 + kRadixBins * kRadixCopies * 4 + 9 * nb8);
+    rc = grab(&ptr, kMaxScanBlocks * 8 + kRadixWords * 4 + 9 * nb8);
     if (rc) { daic_problem_destroy(p.release()); return rc; }
     at = static_cast<char*>(ptr);
     auto next = [&](size_t bytes) { char* q = at; at += bytes; return q; };
     a.blk_small = reinterpret_cast<uint32_t*>(next(kMaxScanBlocks * 4));
     a.blk_large = reinterpret_cast<uint32_t*>(next(kMaxScanBlocks * 4));
-    a.rhist = reinterpret_cast<uint32_t*>(next(kRadixBins * kRadixCopies * 4));
+    a.rhist = reinterpret_cast<uint32_t*>(next(kRadixWords * 4));
     a.off_ties = reinterpret_cast<uint64_t*>(next(nb8));
     a.blk_act = reinterpret_cast<uint64_t*>(next(nb8));
     a.blk_push = reinterpret_cast<uint64_t*>(next(nb8));
