@@ -1095,12 +1095,16 @@ __global__ __launch_bounds__(256) void k_claim(KArgs a) {
   double gain = 0.0;  // learned runs (update rounds tracked): priority realized by the selected vertices
   const bool track = !DRY && a.last_upd != nullptr;
 
-  // Dense rounds without tie counting (sum problems): no bins and no block
-  // scans, so a thread takes four vertices per step with every load of the
-  // four in flight together (the general loop below waits on each vertex).
+  // Dense rounds of sum problems: no bins, so a thread takes four vertices
+  // per step with every load of the four in flight together and, where ties
+  // are ranked, one block scan for them (the general loop below waits on each
+  // vertex, its row and its scan). RMAT-22, a tenth selected by rank: 41.8 ->
+  // 37.6 us; with blocks of up to 512 vertices, of which four steps hold half
+  // or less, the rows of the vertices not selected cost more than they hide
+  // (RMAT-20: 13.2 -> 15.2 us), so ranked ties stay with the general loop
   bool fast = false;
   if constexpr (!DRY && Tr<ST>::sum) {
-    fast = pull && mode != 2;
+    fast = pull && (mode != 2 || a.per_block > 512);
     if (fast) {
       S* vw = static_cast<S*>(a.v);
       S* dw = static_cast<S*>(a.dv);
@@ -1109,7 +1113,8 @@ __global__ __launch_bounds__(256) void k_claim(KArgs a) {
         S vj[4], dj[4];
         float sc[4], cj[4];
         uint64_t r0[4], r1[4];
-        uint32_t pj[4];
+        uint32_t pj[4], tie[4] = {0, 0, 0, 0}, tie_tot[4] = {0, 0, 0, 0};
+        Key key[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const uint64_t j = min(base + threadIdx.x + 256 * u, hi - 1);
@@ -1122,20 +1127,25 @@ __global__ __launch_bounds__(256) void k_claim(KArgs a) {
           pj[u] = a.perm[j];
         }
 #pragma unroll
+        for (int u = 0; u < 4; ++u)
+          key[u] = base + threadIdx.x + 256 * u < hi ? sel_key_loaded<ST>(a, vj[u], dj[u], sc[u]) : (Key)0;
+        if (mode == 2) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) tie[u] = (key[u] != 0 && key[u] == tau) ? 1u : 0u;
+          block_excl_scan<4>(tie, tie_tot);
+        }
+#pragma unroll
         for (int u = 0; u < 4; ++u) {
           const uint64_t j = base + threadIdx.x + 256 * u;
           if (j >= hi) break;
-          Key key = prio_key<ST>(vj[u], dj[u]);
-          if (a.score != nullptr && key != 0) {  // as sel_key
-            const uint32_t bits = __float_as_uint(prio_value<ST>(vj[u], dj[u]) * sc[u]);
-            key = (Key)(bits == 0 ? 1u : bits);
-          }
           bool sel = false;
-          if (key != 0) {
+          if (key[u] != 0) {
             if (mode == 0) sel = true;
-            else if (mode == 1) sel = key >= tau;
+            else if (mode == 1) sel = key[u] >= tau;
+            else if (mode == 2) sel = key[u] > tau || (key[u] == tau && tie_base + ties_seen + tie[u] < ties_left);
             else sel = j / a.rr_chunk == tau;
           }
+          ties_seen += tie_tot[u];
           const uint64_t deg = r1[u] - r0[u];
           bool send = false;
           S mu{};
