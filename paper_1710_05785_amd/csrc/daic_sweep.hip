@@ -40,6 +40,8 @@
 
 namespace daic {
 
+constexpr uint32_t kSweepFinishGrid = 2048;  // workgroups of k_sweep_tile_finish (at most)
+
 struct SweepArgs {
   Ctl* ctl;
   uint64_t n;
@@ -63,10 +65,12 @@ struct SweepArgs {
   const uint32_t* rv;         // vertices with in-edges, grouped by block, ids ascending
   const uint32_t* roff;       // [P+1]
   const double* coef_le;      // [n] by position: sum of |w| to out-neighbours in blocks <= own
+  const double* coef_t;       // the same by target, for the tiles' claims (null otherwise)
   double* part_r;             // residual partials per grid block
   uint64_t* part_n;
   uint64_t* part_a;           // claim partials per grid block: activations, messages
   uint64_t* part_m;
+  const uint32_t* poff;       // tiles: block c's workgroups have partials [poff[c], poff[c+1])
   uint32_t claim_blocks;      // grid of k_sweep_claim
 };
 
@@ -81,6 +85,9 @@ struct SweepState {
   TileGraph tiles;
   TileArgs ta{};
   std::vector<uint32_t> tile_off, split_off;  // [P+1]
+  uint32_t finish_grid(uint32_t c) const {    // workgroups of k_sweep_tile_finish for block c
+    return (uint32_t)std::min<uint64_t>((uint64_t)(split_off[c + 1] - split_off[c]) * (ta.tw / 256), kSweepFinishGrid);
+  }
   std::vector<void*> allocs;
   SweepArgs a{};
   // targets numbered by in-degree octave within each block (the tiles'
@@ -94,7 +101,6 @@ struct SweepState {
 namespace {
 
 constexpr uint32_t kResGrid = 2048;
-constexpr uint32_t kSweepFinishGrid = 2048;  // workgroups of k_sweep_tile_finish (at most)
 
 // Block c: streamed pull of the block's targets. An in-edge from a source
 // at position s reads the base published in this sweep when s lies in an
@@ -132,48 +138,79 @@ __global__ __launch_bounds__(256) void k_sweep_stream(SweepArgs a, uint32_t c, u
   }
 }
 
-// The claim of vertex j in its block's round: d = its delta with this
-// round's received sum included (dv_old is the delta before the pull). A
-// nonzero delta is folded into v (Kahan for the compensated state) and its
-// message base published into the slot of this sweep (0 when silent; only
-// vertices with out-edges have readers).
-template <int ST, int G>
-__device__ __forceinline__ void sweep_claim_vertex(const SweepArgs& a, uint32_t j, typename Tr<ST>::S d,
-                                                   typename Tr<ST>::S dv_old, uint64_t cur, uint64_t& act,
-                                                   uint64_t& pushed) {
+// What the claim of a vertex reads, loaded before its received sum is known.
+template <int ST>
+struct SweepVertex {
   using S = typename Tr<ST>::S;
-  S* mu2 = static_cast<S*>(a.mu2);
+  S dv, v, av;
+  float c;
+  uint32_t r0, r1, pj;
+  double coef;
+};
+
+template <int ST, int G>
+__device__ __forceinline__ SweepVertex<ST> sweep_load(const SweepArgs& a, uint64_t j) {
+  using S = typename Tr<ST>::S;
+  SweepVertex<ST> x;
+  x.dv = static_cast<const S*>(a.dv)[j];
+  x.v = static_cast<const S*>(a.v)[j];
+  x.av = G != DAIC_G_DEG_SCALE && a.alpha_pv ? static_cast<const S*>(a.alpha_pv)[j] : (S)0;
+  x.c = Tr<ST>::kahan ? a.c[j] : 0.f;
+  x.r0 = a.row[j];
+  x.r1 = a.row[j + 1];
+  x.pj = a.perm[j];
+  x.coef = a.coef_t ? a.coef_t[j] : 0.0;
+  return x;
+}
+
+// What a thread's claims add to its round's totals.
+struct SweepSums {
+  uint64_t act = 0, pushed = 0, pending = 0;
+  double r = 0.0;
+};
+
+// The claim of vertex j in its block's round: d = its delta with this
+// round's received sum included. A nonzero delta is folded into v (Kahan for
+// the compensated state) and its message base published into the slot of
+// this sweep (0 when silent; only vertices with out-edges have readers).
+template <int ST, int G>
+__device__ __forceinline__ void sweep_claim_vertex(const SweepArgs& a, uint64_t j, const SweepVertex<ST>& x,
+                                                   typename Tr<ST>::S d, uint64_t cur, SweepSums& sum) {
+  using S = typename Tr<ST>::S;
   S* v = static_cast<S*>(a.v);
   S* dv = static_cast<S*>(a.dv);
-  const uint32_t deg = a.row[j + 1] - a.row[j];
+  const uint32_t deg = x.r1 - x.r0;
   S mu = (S)0;
   if (d != (S)0) {
     dv[j] = (S)0;
-    const S vj = v[j];
     if constexpr (Tr<ST>::kahan) {
       // compensated fold (Kahan 1965), as in the round kernels
 #pragma clang fp contract(off)
-      const float cj = a.c[j];
-      const float y = d - cj;
-      const float t = vj + y;
-      a.c[j] = (t - vj) - y;
+      const float y = d - x.c;
+      const float t = x.v + y;
+      a.c[j] = (t - x.v) - y;
       v[j] = t;
     } else {
-      v[j] = vj + d;
+      v[j] = x.v + d;
     }
     double coef;
     if constexpr (G == DAIC_G_DEG_SCALE) {
       coef = deg ? a.alpha / (double)deg : 0.0;
     } else {
-      coef = a.alpha_pv ? (double)static_cast<const S*>(a.alpha_pv)[j] : a.alpha;
+      coef = a.alpha_pv ? (double)x.av : a.alpha;
     }
     mu = (S)(coef * (double)d);
-    act += 1;
-    pushed += deg;
-  } else if (dv_old != (S)0) {
+    sum.act += 1;
+    sum.pushed += deg;
+  } else if (x.dv != (S)0) {
     dv[j] = (S)0;  // the received sum cancelled the delta
   }
-  if (deg) mu2[cur + a.perm[j]] = mu;
+  if (deg) {
+    static_cast<S*>(a.mu2)[cur + x.pj] = mu;
+    const double m = fabs((double)mu);
+    sum.r += m * x.coef;
+    sum.pending += m > 0.0 ? 1 : 0;
+  }
 }
 
 // Block c: fold the received sum (dv, filled by k_sweep_stream) into the
@@ -182,98 +219,116 @@ __device__ __forceinline__ void sweep_claim_vertex(const SweepArgs& a, uint32_t 
 // slots (sweeps 1 and 2) they are skipped.
 template <int ST, int G>
 __global__ __launch_bounds__(256) void k_sweep_claim(SweepArgs a, uint32_t c) {
-  using S = typename Tr<ST>::S;
   Ctl* ctl = a.ctl;
   if (ctl_halted(ctl)) return;
   const uint64_t k = ctl->rounds / a.P;
   const uint64_t cur = (k & 1) * a.n;
-  const S* dv = static_cast<const S*>(a.dv);
   const bool all = k < 3;
   const uint64_t vb = all ? a.voff[c] : a.roff[c], ve = all ? a.voff[c + 1] : a.roff[c + 1];
-  uint64_t act = 0, pushed = 0;
+  SweepSums sum;
   for (uint64_t i = vb + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ve;
        i += (uint64_t)gridDim.x * blockDim.x) {
     const uint32_t j = all ? (uint32_t)i : a.rv[i];
-    const S d = dv[j];
-    sweep_claim_vertex<ST, G>(a, j, d, d, cur, act, pushed);
+    const SweepVertex<ST> x = sweep_load<ST, G>(a, j);
+    sweep_claim_vertex<ST, G>(a, j, x, x.dv, cur, sum);
   }
-  act = block_sum256(act);
-  pushed = block_sum256(pushed);
+  sum.act = block_sum256(sum.act);
+  sum.pushed = block_sum256(sum.pushed);
   if (threadIdx.x == 0) {
-    a.part_a[blockIdx.x] = act;
-    a.part_m[blockIdx.x] = pushed;
+    a.part_a[blockIdx.x] = sum.act;
+    a.part_m[blockIdx.x] = sum.pushed;
   }
 }
 
-// Block c through the tiled in-edges (sources in sweep numbers): tiles
-// [tb, te) of the block's partitions; the message of an in-edge from source
+// Block c of a sweep over tiles does not run once the run has ended or the
+// round limit lies before it (the round count is that of the sweep's start).
+__device__ __forceinline__ bool sweep_skips(const Ctl* ctl, uint32_t c) {
+  return ctl_halted(ctl) || ctl->rounds + c >= ctl->max_rounds;
+}
+
+template <int NW>
+__device__ __forceinline__ void sweep_store_sums(const SweepArgs& a, uint32_t at, const SweepSums& sum) {
+  uint64_t x[3] = {sum.act, sum.pushed, sum.pending};
+  double r = sum.r;
+  block_sums<NW>(x, r);
+  if (threadIdx.x == 0) {
+    a.part_a[at] = x[0];
+    a.part_m[at] = x[1];
+    a.part_n[at] = x[2];
+    a.part_r[at] = r;
+  }
+}
+
+// Block c through the tiled in-edges (sources in sweep numbers), one tile of
+// the block's partitions to a workgroup, from tile tb on; the message of an in-edge from source
 // s is the base published in this sweep when s < c B, else the previous
 // sweep's (times the weight for EDGE_SCALE), summed per target in FP64 LDS
 // accumulators. A workgroup then claims the targets of an unsplit partition
 // with their sums included (every vertex of the block lies in one partition,
 // so this is the block's claim); the tiles of split partitions store slots,
-// whose targets k_sweep_tile_finish claims. The update counts go to the
-// claim partials (tile workgroups first, then the finishing workgroups).
+// whose targets k_sweep_tile_finish claims. The workgroups' sums, the sweep's
+// residual among them, go to the block's partials (tile workgroups first,
+// then the finishing workgroups), and the round count stays at the sweep's
+// start: kernels that counted each block's round and read every base again
+// for the residual took 4.7 us of a block and 17 us of a sweep (RMAT-22, four
+// blocks: 274 -> 248 us of kernels a sweep).
 template <int ST, int G, uint32_t NT>
-__global__ __launch_bounds__(NT) void k_sweep_tile(SweepArgs a, TileArgs t, uint32_t c, uint32_t tb, uint32_t te) {
+__global__ __launch_bounds__(NT) void k_sweep_tile(SweepArgs a, TileArgs t, uint32_t c, uint32_t tb) {
   using S = typename Tr<ST>::S;
   Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl)) return;
-  uint64_t act = 0, pushed = 0;
+  if (sweep_skips(ctl, c)) return;
   __shared__ double acc[TileShape<NT>::cap];
   const uint32_t tid = threadIdx.x;
   const uint64_t k = ctl->rounds / a.P;
   const uint64_t cur = (k & 1) * a.n, prev = ((k + 1) & 1) * a.n, lo = (uint64_t)c * a.B;
   const S* mu2 = static_cast<const S*>(a.mu2);
   const S* wt = static_cast<const S*>(t.wtile);
-  const S* dv = static_cast<const S*>(a.dv);
   auto msg = [&](uint32_t src, uint32_t e) -> double {
     double x = (double)mu2[(src < lo ? cur : prev) + src];
     if constexpr (G == DAIC_G_EDGE_SCALE) x *= (double)wt[e];
     return x;
   };
   auto add = [&](uint32_t l, double x) { atomicAdd(&acc[l], x); };  // adding 0 leaves a sum as it is
-  for (uint64_t pos = tb + blockIdx.x; pos < te; pos += gridDim.x) {
-    const uint32_t tile = t.tile_order[pos];
-    const uint32_t part = t.tile_part[tile], e0 = t.tile_e[tile], e1 = t.tile_e[tile + 1], slot = t.tile_slot[tile];
-    for (uint32_t i = tid; i < t.tw; i += NT) acc[i] = 0.0;
-    __syncthreads();
-    tile_walk<NT, G != DAIC_G_EDGE_SCALE, double>(t, e0, e1, msg, add);
-    __syncthreads();
-    const uint64_t base = (uint64_t)part * t.tw;
-    const uint32_t count = (uint32_t)min((uint64_t)t.tw, a.n - base);
-    if (slot == 0xFFFFFFFFu) {
-      for (uint32_t i = tid; i < count; i += NT) {
-        const S old = dv[base + i];
-        sweep_claim_vertex<ST, G>(a, (uint32_t)(base + i), (S)((double)old + acc[i]), old, cur, act, pushed);
+  const uint32_t tile = t.tile_order[tb + blockIdx.x];
+  const uint32_t part = t.tile_part[tile], e0 = t.tile_e[tile], e1 = t.tile_e[tile + 1], slot = t.tile_slot[tile];
+  for (uint32_t i = tid; i < t.tw; i += NT) acc[i] = 0.0;
+  __syncthreads();
+  tile_walk<NT, G != DAIC_G_EDGE_SCALE, double>(t, e0, e1, msg, add);
+  __syncthreads();
+  SweepSums sum;
+  const uint64_t base = (uint64_t)part * t.tw;
+  const uint32_t count = (uint32_t)min((uint64_t)t.tw, a.n - base);
+  if (slot == 0xFFFFFFFFu) {
+    // four targets per step, their loads in flight together
+    for (uint32_t i0 = tid; i0 < count; i0 += 4 * NT) {
+      SweepVertex<ST> x[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) x[u] = sweep_load<ST, G>(a, base + min(i0 + u * NT, count - 1));
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        const uint32_t i = i0 + u * NT;
+        if (i < count) sweep_claim_vertex<ST, G>(a, base + i, x[u], (S)((double)x[u].dv + acc[i]), cur, sum);
       }
-    } else {
-      SlotT<ST>* dst = reinterpret_cast<SlotT<ST>*>(t.pbuf) + (uint64_t)slot * t.tw;
-      for (uint32_t i = tid; i < count; i += NT) dst[i] = (SlotT<ST>)acc[i];
     }
-    __syncthreads();
+  } else {
+    SlotT<ST>* dst = reinterpret_cast<SlotT<ST>*>(t.pbuf) + (uint64_t)slot * t.tw;
+    for (uint32_t i = tid; i < count; i += NT) dst[i] = (SlotT<ST>)acc[i];
   }
-  act = block_sum_waves<NT / 64>(act);
-  pushed = block_sum_waves<NT / 64>(pushed);
-  if (threadIdx.x == 0) {
-    a.part_a[blockIdx.x] = act;
-    a.part_m[blockIdx.x] = pushed;
-  }
+  sweep_store_sums<NT / 64>(a, a.poff[c] + blockIdx.x, sum);
 }
 
 // Targets of block c's split partitions [sb, se): their slots added in tile
-// order (FP64), then claimed with the sum included. Partials at
-// part_a/part_m[poff + workgroup].
+// order (FP64), then claimed with the sum included. Their workgroups'
+// partials follow those of the block's `tiles` tile workgroups.
 template <int ST, int G>
 __global__ __launch_bounds__(256) void k_sweep_tile_finish(SweepArgs a, TileArgs t, uint32_t sb, uint32_t se,
-                                                           uint32_t poff) {
+                                                           uint32_t c, uint32_t tiles) {
   using S = typename Tr<ST>::S;
   Ctl* ctl = a.ctl;
-  if (ctl_halted(ctl)) return;
-  const S* dv = static_cast<const S*>(a.dv);
+  if (sweep_skips(ctl, c)) return;
   const SlotT<ST>* pbuf = reinterpret_cast<const SlotT<ST>*>(t.pbuf);
   const uint64_t cur = ((ctl->rounds / a.P) & 1) * a.n;
-  uint64_t act = 0, pushed = 0;
+  SweepSums sums;
   const uint32_t chunks = t.tw / 256;
   for (uint64_t item = (uint64_t)sb * chunks + blockIdx.x; item < (uint64_t)se * chunks; item += gridDim.x) {
     const uint64_t sp = item / chunks;
@@ -282,6 +337,7 @@ __global__ __launch_bounds__(256) void k_sweep_tile_finish(SweepArgs a, TileArgs
     const uint64_t base = (uint64_t)part * t.tw + chunk * 256;
     if (base + threadIdx.x >= a.n) continue;
     const uint32_t i = chunk * 256 + threadIdx.x;
+    const SweepVertex<ST> own = sweep_load<ST, G>(a, base + threadIdx.x);
     double sum = 0.0;
     for (uint32_t q = k0; q < k1; q += 16) {
       double x[16];
@@ -291,21 +347,60 @@ __global__ __launch_bounds__(256) void k_sweep_tile_finish(SweepArgs a, TileArgs
       for (uint32_t u = 0; u < 16; ++u)
         if (q + u < k1) sum += x[u];
     }
-    const uint32_t j = (uint32_t)(base + threadIdx.x);
-    const S old = dv[j];
-    sweep_claim_vertex<ST, G>(a, j, (S)((double)old + sum), old, cur, act, pushed);
+    sweep_claim_vertex<ST, G>(a, base + threadIdx.x, own, (S)((double)own.dv + sum), cur, sums);
   }
-  act = block_sum256(act);
-  pushed = block_sum256(pushed);
-  if (threadIdx.x == 0) {
-    a.part_a[poff + blockIdx.x] = act;
-    a.part_m[poff + blockIdx.x] = pushed;
-  }
+  sweep_store_sums<4>(a, a.poff[c] + tiles + blockIdx.x, sums);
 }
 
-// After each round: add the claim's per-block counts to the totals; when the
-// round does not end a sweep, count it and apply the round limit (the sweep's
-// last round is counted by k_sweep_residual_final).
+// End of a sweep over tiles (one block of 1,024 threads): the partials of
+// the blocks that ran (all, or those before the round limit) added in a fixed
+// order, the round count and the stop rule.
+__global__ __launch_bounds__(1024) void k_sweep_end(SweepArgs a) {
+  Ctl* ctl = a.ctl;
+  if (ctl_halted(ctl)) return;
+  const uint64_t rounds = ctl->rounds, left = ctl->max_rounds - rounds;
+  const uint32_t ran = left < a.P ? (uint32_t)left : a.P;
+  const uint32_t count = a.poff[ran];
+  uint64_t x[3] = {0, 0, 0};
+  double r = 0.0;
+  for (uint32_t i0 = threadIdx.x; i0 < count; i0 += 4 * 1024) {
+    uint64_t xa[4], xm[4], xn[4];
+    double xr[4];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t i = min(i0 + u * 1024, count - 1);
+      xa[u] = a.part_a[i];
+      xm[u] = a.part_m[i];
+      xn[u] = a.part_n[i];
+      xr[u] = a.part_r[i];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u)
+      if (i0 + u * 1024 < count) {
+        x[0] += xa[u];
+        x[1] += xm[u];
+        x[2] += xn[u];
+        r += xr[u];
+      }
+  }
+  block_sums<16>(x, r);
+  if (threadIdx.x != 0) return;
+  ctl->activations += x[0];
+  ctl->pushed += x[1];
+  ctl->rounds = rounds + ran;
+  bool done = false;
+  if (ran == a.P) {
+    ctl->r = r;
+    ctl->pending = x[2];
+    done = r <= ctl->eps;
+    ctl->done = done ? 1u : 0u;
+  }
+  ctl->stop = (!done && rounds + ran >= ctl->max_rounds) ? 1u : 0u;
+}
+
+// After each round of the streamed pull: add the claim's per-block counts to
+// the totals; when the round does not end a sweep, count it and apply the
+// round limit (the sweep's last round is counted by k_sweep_residual_final).
 __global__ __launch_bounds__(256) void k_sweep_step(SweepArgs a, int sweep_end, uint32_t nparts) {
   Ctl* ctl = a.ctl;
   if (ctl_halted(ctl)) return;
@@ -326,7 +421,7 @@ __global__ __launch_bounds__(256) void k_sweep_step(SweepArgs a, int sweep_end, 
   }
 }
 
-// End of a sweep: per-workgroup partials of the bound on the pending mass
+// End of a streamed sweep: per-workgroup partials of the bound on the pending mass
 // (k_sweep_residual_final adds them in a fixed order).
 template <int ST>
 __global__ __launch_bounds__(256) void k_sweep_residual(SweepArgs a) {
@@ -478,29 +573,28 @@ template <int ST, int G>
 struct SweepImpl {
   static void round(const SweepState& w, hipStream_t s, uint32_t c) {
     const SweepArgs& a = w.a;
-    uint32_t nparts = a.claim_blocks;
+    const bool end = c + 1 == a.P;
     if (w.tiles.ready) {  // the block's tiles, then its split partitions, each claiming its targets
       const uint32_t tb = w.tile_off[c], te = w.tile_off[c + 1], sb = w.split_off[c], se = w.split_off[c + 1];
-      const uint32_t fg = se > sb ? sgrid((uint64_t)(se - sb) * (w.ta.tw / 256), 1, kSweepFinishGrid) : 0;
+      const uint32_t fg = w.finish_grid(c);
       const SweepArgs& at = w.numbered ? w.ar : w.a;
       if (te > tb) {
         if (w.ta.tw > kNarrowTW)
-          hipLaunchKernelGGL((k_sweep_tile<ST, G, 1024>), dim3(te - tb), dim3(1024), 0, s, at, w.ta, c, tb, te);
+          hipLaunchKernelGGL((k_sweep_tile<ST, G, 1024>), dim3(te - tb), dim3(1024), 0, s, at, w.ta, c, tb);
         else
-          hipLaunchKernelGGL((k_sweep_tile<ST, G, 256>), dim3(te - tb), dim3(256), 0, s, at, w.ta, c, tb, te);
+          hipLaunchKernelGGL((k_sweep_tile<ST, G, 256>), dim3(te - tb), dim3(256), 0, s, at, w.ta, c, tb);
       }
       if (fg)
-        hipLaunchKernelGGL((k_sweep_tile_finish<ST, G>), dim3(fg), dim3(256), 0, s, at, w.ta, sb, se, te - tb);
-      nparts = (te - tb) + fg;
-    } else {
-      // one workgroup per edge block of block c, at most 16384
-      const uint32_t bb = w.block_sb_off[c], be = w.block_sb_off[c + 1];
-      if (be > bb)
-        hipLaunchKernelGGL((k_sweep_stream<ST, G>), dim3(sgrid(be - bb, 1, 16384)), dim3(256), 0, s, a, c, bb, be);
-      hipLaunchKernelGGL((k_sweep_claim<ST, G>), dim3(a.claim_blocks), dim3(256), 0, s, a, c);
+        hipLaunchKernelGGL((k_sweep_tile_finish<ST, G>), dim3(fg), dim3(256), 0, s, at, w.ta, sb, se, c, te - tb);
+      if (end) hipLaunchKernelGGL(k_sweep_end, dim3(1), dim3(1024), 0, s, a);
+      return;
     }
-    const bool end = c + 1 == a.P;
-    hipLaunchKernelGGL(k_sweep_step, dim3(1), dim3(256), 0, s, a, end ? 1 : 0, nparts);
+    // one workgroup per edge block of block c, at most 16384
+    const uint32_t bb = w.block_sb_off[c], be = w.block_sb_off[c + 1];
+    if (be > bb)
+      hipLaunchKernelGGL((k_sweep_stream<ST, G>), dim3(sgrid(be - bb, 1, 16384)), dim3(256), 0, s, a, c, bb, be);
+    hipLaunchKernelGGL((k_sweep_claim<ST, G>), dim3(a.claim_blocks), dim3(256), 0, s, a, c);
+    hipLaunchKernelGGL(k_sweep_step, dim3(1), dim3(256), 0, s, a, end ? 1 : 0, a.claim_blocks);
     if (end) {
       const uint32_t g = sgrid(a.n, 256, kResGrid);
       hipLaunchKernelGGL(k_sweep_residual<ST>, dim3(g), dim3(256), 0, s, a);
@@ -704,20 +798,10 @@ daic_status sweep_setup(daic_problem* p, uint64_t B, hipStream_t s) {
     if (T.n_split) DAIC_HIP(hipMemcpy(sp.data(), T.split_part, T.n_split * 4, hipMemcpyDeviceToHost));
     w->tile_off.assign(P + 1, 0);
     w->split_off.assign(P + 1, 0);
-    uint32_t max_tiles = 0;
     for (uint32_t c = 0; c <= P; ++c) {
       const uint64_t first_part = std::min<uint64_t>((uint64_t)c * B / TW, T.n_part);
       w->tile_off[c] = (uint32_t)(std::lower_bound(tp.begin(), tp.end(), (uint32_t)first_part) - tp.begin());
       w->split_off[c] = (uint32_t)(std::lower_bound(sp.begin(), sp.end(), (uint32_t)first_part) - sp.begin());
-      if (c) max_tiles = std::max(max_tiles, w->tile_off[c] - w->tile_off[c - 1]);
-    }
-    // claim partials of a round: its tile workgroups, then its finishing ones
-    if (max_tiles + kSweepFinishGrid > a.claim_blocks) {
-      void *pa = nullptr, *pm = nullptr;
-      if ((rc = grab(&pa, (max_tiles + kSweepFinishGrid) * 8)) || (rc = grab(&pm, (max_tiles + kSweepFinishGrid) * 8)))
-        return rc;
-      a.part_a = static_cast<uint64_t*>(pa);
-      a.part_m = static_cast<uint64_t*>(pm);
     }
     TileArgs& t = w->ta;
     t.tloc = T.tloc;
@@ -737,6 +821,23 @@ daic_status sweep_setup(daic_problem* p, uint64_t B, hipStream_t s) {
     void* pb = nullptr;
     if ((rc = grab(&pb, std::max<uint64_t>(T.n_slots, 1) * TW * 8))) return rc;
     t.pbuf = static_cast<double*>(pb);
+    // partials of a sweep: for each block its tile workgroups, then its
+    // finishing ones
+    std::vector<uint32_t> poff(P + 1, 0);
+    for (uint32_t c = 0; c < P; ++c) poff[c + 1] = poff[c] + (w->tile_off[c + 1] - w->tile_off[c]) + w->finish_grid(c);
+    const uint64_t np = std::max<uint32_t>(poff[P], 1);
+    void *ct = nullptr, *po = nullptr, *pr = nullptr, *pn = nullptr, *pa = nullptr, *pm = nullptr;
+    if ((rc = grab(&ct, n * 8)) || (rc = grab(&po, (P + 1) * 4)) || (rc = grab(&pr, np * 8)) ||
+        (rc = grab(&pn, np * 8)) || (rc = grab(&pa, np * 8)) || (rc = grab(&pm, np * 8)))
+      return rc;
+    DAIC_HIP(hipMemcpy(po, poff.data(), (P + 1) * 4, hipMemcpyHostToDevice));
+    perm_gather(a.coef_le, ct, 8, T.permP ? T.permP : a.perm, n, s);
+    a.coef_t = static_cast<const double*>(ct);
+    a.poff = static_cast<const uint32_t*>(po);
+    a.part_r = static_cast<double*>(pr);
+    a.part_n = static_cast<uint64_t*>(pn);
+    a.part_a = static_cast<uint64_t*>(pa);
+    a.part_m = static_cast<uint64_t*>(pm);
     if (T.tinv) {
       SweepArgs& r = w->ar;
       r = a;
