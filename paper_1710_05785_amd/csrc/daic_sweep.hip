@@ -339,14 +339,7 @@ __global__ __launch_bounds__(256) void k_sweep_tile_finish(SweepArgs a, TileArgs
     const uint32_t i = chunk * 256 + threadIdx.x;
     const SweepVertex<ST> own = sweep_load<ST, G>(a, base + threadIdx.x);
     double sum = 0.0;
-    for (uint32_t q = k0; q < k1; q += 16) {
-      double x[16];
-#pragma unroll
-      for (uint32_t u = 0; u < 16; ++u) x[u] = (double)pbuf[(uint64_t)min(q + u, k1 - 1) * t.tw + i];
-#pragma unroll
-      for (uint32_t u = 0; u < 16; ++u)
-        if (q + u < k1) sum += x[u];
-    }
+    each_slot(pbuf, t.tw, i, k0, k1, [&](SlotT<ST> x) { sum += (double)x; });
     sweep_claim_vertex<ST, G>(a, base + threadIdx.x, own, (S)((double)own.dv + sum), cur, sums);
   }
   sweep_store_sums<4>(a, a.poff[c] + tiles + blockIdx.x, sums);
