@@ -44,8 +44,8 @@ constexpr uint32_t kSwHubChunk = 256;
 // A batch that those sizes would cut into few items gets smaller ones, so
 // that about kItemsWanted workgroups (eight for each of the 256 CUs) share a
 // round: 120,000 vertices and 960,000 edges made 30 items and a round of
-// 0.61 ms of two kernels that left most CUs idle, against 0.13 ms in 2,100
-// items. At least four passes of a workgroup's 16 vertices per item, and hub
+// 0.67 ms that left most CUs idle, against 75 us in 2,100 items (hub chunks
+// cut with them). At least four passes of a workgroup's 16 vertices per item, and hub
 // chunks of at least 64 in-edges.
 constexpr uint32_t kItemsWanted = 2048;
 constexpr uint32_t kItemVertsMin = 64;

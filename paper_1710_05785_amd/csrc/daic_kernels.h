@@ -697,7 +697,7 @@ __device__ __forceinline__ Key block_kth_sampled(KthScratch& s, uint32_t rank, u
 // A2 (sampled): threshold = the rank-th largest of S sampled keys; a
 // threshold of 0 (no positive sample) selects every pending vertex. One
 // workgroup of 1,024 threads, up to four samples each: the draws and the
-// selection in one kernel take 9 us (S = 4,096), where a kernel that drew
+// selection in one kernel take 12 us (S = 4,096), where a kernel that drew
 // them and one whose 64 workgroups ranked all pairs took 3 and 16-20 us.
 // ---------------------------------------------------------------------------
 template <int ST>
