@@ -1297,7 +1297,7 @@ static double kernel_bytes(const daic_problem* p, const char* name, const Ctl& c
     const bool sum = p->st == ST_F64 || p->st == ST_F32 || p->st == ST_F32K;
     const double tw = (double)(1ull << T.tbits);
     const double split_targets = (double)T.n_split * tw;
-    const double slots = (double)T.n_slots * tw * (sum ? (double)slot_size(p->st) : S);
+    const double slots = (double)T.n_slots * tw * (sum ? (double)slot_size(p->st, 1u << T.tbits) : S);
     const double wb = p->gk == DAIC_G_EDGE_SCALE ? S : p->gk == DAIC_G_EDGE_ADD ? (p->st == ST_U32 ? 4.0 : 8.0) : 0.0;
     const double fin = (sum ? 2.0 : 3.0) * S;
     if (!std::strcmp(name, "pull_tile"))
@@ -1321,7 +1321,7 @@ static double kernel_bytes(const daic_problem* p, const char* name, const Ctl& c
     const double fin = 2.0 * S + 2.0 * S + kahan + 2.0 * R + 4.0 + S;
     const double tw = (double)(1ull << T.tbits);
     const double split_targets = (double)T.n_split * tw;  // upper bound (the last partition may be short)
-    const double slots = (double)T.n_slots * tw * (double)slot_size(p->st);
+    const double slots = (double)T.n_slots * tw * (double)slot_size(p->st, 1u << T.tbits);
     if (name[5] == 'p')
       return (double)p->g->dev.m * (2.0 + (p->gk == DAIC_G_EDGE_SCALE ? S : 0.0)) + (double)T.n_pairs * (4.0 + S) +
              (double)T.n_seg * 4.0 + (double)T.n_tiles * 12.0 + std::max(0.0, n - split_targets) * fin + slots;

@@ -42,7 +42,7 @@ struct TileArgs {
   const uint32_t* tile_order;  // launch order: a workgroup takes tiles tile_order[workgroup], [workgroup + grid], ...
   const uint32_t* split_part;
   const uint32_t* split_slot;
-  double* pbuf;               // [n_slots][tw] partial sums of the tiles of split partitions (SlotT<ST>)
+  double* pbuf;               // [n_slots][tw] partial sums of the tiles of split partitions (RoundSlotT; sweeps SlotT)
   uint64_t m, n_tiles, n_split, n_seg;
   uint32_t tw;                // partition width (a power of two, 1,024..kTileT)
   uint32_t pull_grid;         // workgroups that walk the tiles
@@ -127,7 +127,11 @@ __device__ __forceinline__ void tile_finish_targets(const KArgs& a, typename Tr<
 // FP64 otherwise. The slots are added in FP64.
 template <int ST>
 using SlotT = typename std::conditional<ST == ST_F32 || ST == ST_F32K, float, double>::type;
-inline uint32_t slot_size(int st) { return st == ST_F32 || st == ST_F32K ? 4u : 8u; }
+// Narrow partitions, of which many are split, keep FP64 slots: their sums are
+// rounded where those of unsplit ones are.
+template <int ST, uint32_t NT>
+using RoundSlotT = typename std::conditional<NT == 1024, SlotT<ST>, double>::type;
+inline uint32_t slot_size(int st, uint32_t tw) { return (st == ST_F32 || st == ST_F32K) && tw > kNarrowTW ? 4u : 8u; }
 
 // f(slot value) for entry i of the slots [k0, k1) of a split partition, in
 // order: four loads in flight for up to four slots, else 16. Partitions split
@@ -259,8 +263,9 @@ __device__ __forceinline__ void tile_pull_block(const KArgs& a, const TileArgs& 
         tile_finish_targets<ST, G, FUSED>(a, mu_out, base, count, tid, kTileThreads,
                                           [&](uint32_t i) { return acc[i]; }, r_part, act, pushed);
       } else {
-        SlotT<ST>* dst = reinterpret_cast<SlotT<ST>*>(t.pbuf) + (uint64_t)slot * t.tw;
-        for (uint32_t i = tid; i < count; i += kTileThreads) dst[i] = (SlotT<ST>)acc[i];
+        using Slot = RoundSlotT<ST, NT>;
+        Slot* dst = reinterpret_cast<Slot*>(t.pbuf) + (uint64_t)slot * t.tw;
+        for (uint32_t i = tid; i < count; i += kTileThreads) dst[i] = (Slot)acc[i];
       }
       __syncthreads();
     }
@@ -288,7 +293,7 @@ __global__ __launch_bounds__(NT) void k_tile_pull(KArgs a, TileArgs t) {
 // Targets of split partitions: a work item is 256 consecutive targets of one
 // split partition; their slots are added in tile order while the targets'
 // operands load (PageRank rounds on RMAT-20: 16.6 -> 15.4 us, 300,000
-// vertices: 10.0 -> 9.0).
+// vertices: 10.0 -> 9.0; with their slots in FP64 15.9 and 9.8).
 template <int ST, int G, bool FUSED>
 __device__ __forceinline__ void tile_finish_block(const KArgs& a, const TileArgs& t, uint32_t nblocks) {
   using S = typename Tr<ST>::S;
@@ -296,7 +301,6 @@ __device__ __forceinline__ void tile_finish_block(const KArgs& a, const TileArgs
     Ctl* ctl = a.ctl;
     const bool odd = FUSED && ((ctl->rounds - ctl->fuse_base) & 1) != 0;
     S* mu_out = static_cast<S*>(odd ? a.mu_pi : a.mu_pi2);
-    const SlotT<ST>* pbuf = reinterpret_cast<const SlotT<ST>*>(t.pbuf);
     const uint32_t tid = threadIdx.x;
     const uint32_t kChunks = t.tw / 256;
     double r_part = 0.0;
@@ -310,7 +314,10 @@ __device__ __forceinline__ void tile_finish_block(const KArgs& a, const TileArgs
       const uint32_t count = (uint32_t)min((uint64_t)256, a.n - base);
       const auto sum = [&](uint32_t i) {
         double x = 0.0;
-        each_slot(pbuf, t.tw, chunk * 256 + i, k0, k1, [&](SlotT<ST> y) { x += (double)y; });
+        if (t.tw > kNarrowTW)
+          each_slot(reinterpret_cast<const SlotT<ST>*>(t.pbuf), t.tw, chunk * 256 + i, k0, k1,
+                    [&](SlotT<ST> y) { x += (double)y; });
+        else each_slot(t.pbuf, t.tw, chunk * 256 + i, k0, k1, [&](double y) { x += y; });
         return x;
       };
       tile_finish_targets<ST, G, FUSED, 1>(a, mu_out, base, count, tid, 256, sum, r_part, act, pushed);
