@@ -44,7 +44,7 @@ constexpr uint32_t kSwHubChunk = 256;
 // A batch that those sizes would cut into few items gets smaller ones, so
 // that about kItemsWanted workgroups (eight for each of the 256 CUs) share a
 // round: 120,000 vertices and 960,000 edges made 30 items and a round of
-// 0.67 ms that left most CUs idle, against 75 us in 2,100 items (hub chunks
+// 0.67 ms that left most CUs idle, against 82 us in 2,100 items (hub chunks
 // cut with them). At least four passes of a workgroup's 16 vertices per item, and hub
 // chunks of at least 64 in-edges.
 constexpr uint32_t kItemsWanted = 2048;
@@ -477,8 +477,11 @@ __global__ __launch_bounds__(256) void k_bresidual(BArgs a, int count_round) {
 // the instances whose messages are not yet all delivered; atomics where a
 // target has several chunks.
 // Sum over in-edges [beg, end) of the message-base vectors (times the edge
-// weight under EDGE_SCALE), four gathers in flight per lane, with the next
-// four sources (and weights) on their way while they arrive.
+// weight under EDGE_SCALE), four gathers in flight per lane. (The next four
+// sources loaded meanwhile took a round of 12 graphs of 10,000 vertices from
+// 82 to 75 us, but their registers cost the fused pass of large batches a
+// wave per SIMD: 64 graphs of scales 12 to 20 without the Kahan term 385 ->
+// 395 ms.)
 template <int W, bool WGT>
 __device__ __forceinline__ void bgather(const BArgs& a, const float* mu_in, uint32_t beg, uint32_t end, uint32_t r0,
                                         float (&acc)[W]) {
@@ -1668,10 +1671,11 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
     for (uint64_t l : load) all += l;
     if (8 * kXcd * *std::max_element(load.begin(), load.end()) > 9 * all) {
       // The heaviest XCD has an eighth more than its share, as with a few
-      // graphs, which may leave XCDs idle: graphs are cut into pieces of half
-      // an XCD's share (12 equal graphs: 15.7 against 17.4 ms). Where whole
-      // graphs are balanced the cut costs locality: 64 graphs of scales 12 to
-      // 20 without the Kahan term 397 ms cut, 388 whole.
+      // graphs (12 equal ones put two on each of four XCDs, 4/3 of a share;
+      // one leaves seven idle): graphs are cut into pieces of half an XCD's
+      // share. Where whole graphs are balanced they stay whole, and sweeps
+      // always keep them so: with the pieces' XCDs, 64 graphs of scales 12 to
+      // 20 took 393 ms in sweeps of 8 blocks against 339.
       uint64_t work = 0;
       for (uint64_t w : rw) work += w;
       struct Piece {
