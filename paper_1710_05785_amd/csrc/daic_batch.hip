@@ -50,6 +50,9 @@ constexpr uint32_t kSwHubChunk = 256;
 constexpr uint32_t kItemsWanted = 2048;
 constexpr uint32_t kItemVertsMin = 64;
 constexpr uint32_t kHubChunkMin = 64;
+constexpr uint32_t kHubRows = 16;      // rows of the hub table that a workgroup takes together
+constexpr uint32_t kNoRow = 0xFFFFFFFFu;
+static_assert(kBChunk <= kHubRows * kHubChunkMin, "a piece lies in one workgroup");
 constexpr uint32_t kHubDeg = 64;       // default in-degree above which a target is a hub
 
 // Round modes: 0 = sparse round (claim, push, residual); 1 = the claim that
@@ -124,7 +127,8 @@ struct BArgs {
   // fused dense rounds: in-edges of hub targets (in-degree > hub_deg) are
   // summed by a chunked kernel before the fused pass
   uint32_t hub_deg;
-  uint32_t hub_chunk;         // in-edges per hub item
+  uint32_t hub_chunk;         // in-edges per row of the hub table (ht, hc),
+  uint32_t hub_piece;         //   and of a piece: its rows lie in one workgroup (see hub_items)
   const uint32_t* ht;         // hub items (target, chunk)
   const uint32_t* hc;
   uint64_t n_hub;
@@ -472,10 +476,6 @@ __global__ __launch_bounds__(256) void k_bresidual(BArgs a, int count_round) {
   // retired after the kernel: k_bretire_sparse
 }
 
-// Dense phase, hub targets (in-degree > hub_deg): one item per (target, chunk
-// of kBChunk in-edges) adds the previous round's message bases into dv, for
-// the instances whose messages are not yet all delivered; atomics where a
-// target has several chunks.
 // Sum over in-edges [beg, end) of the message-base vectors (times the edge
 // weight under EDGE_SCALE), four gathers in flight per lane. (The next four
 // sources loaded meanwhile took a round of 12 graphs of 10,000 vertices from
@@ -565,10 +565,101 @@ __global__ void k_bstep(BArgs a) {
   ctl->rounds += 1;
 }
 
+// Hub targets (in-degree > hub_deg) of a dense round or of a sweep's block:
+// adds gather(t, in-edges [beg, end)) into dv of target t, for the instances
+// whose messages are not yet all delivered, over the rows [i0, i1) of the hub
+// table (hub_table). A target of one piece (hub_piece in-edges) is stored by
+// one thread group, pieces of larger ones are added by atomics. A piece of
+// several chunks (batches of few workgroups) has its rows side by side in one
+// workgroup, which adds them in LDS in chunk order: with an atomic per chunk
+// targets of 129 to 1,024 in-edges were summed in another order, and so to
+// other last bits, on each run. (A round of 12 graphs of 10,000 vertices x 64:
+// 81 us with the atomics, 75 so; two graphs of 600 x 8, where nothing fills
+// the chip: 36 and 39; sweeps in four blocks 50 and 51.)
+template <int LPV, typename Gather>
+__device__ __forceinline__ void hub_items(const BArgs& a, uint64_t i0, uint64_t i1, const Gather& gather) {
+  constexpr int W = kR / LPV;
+  constexpr int IPB = 256 / LPV;
+  const uint32_t sub = threadIdx.x / LPV;
+  const uint32_t r0 = (threadIdx.x % LPV) * W;
+  // the chunk of row i: false when it has none, or no instance to deliver to
+  auto chunk = [&](uint64_t i, bool(&live)[W], float(&acc)[W]) {
+#pragma unroll
+    for (int k = 0; k < W; ++k) acc[k] = 0.0f;
+    const uint32_t t = a.ht[i];
+    if (t == kNoRow) return false;
+    const uint8_t* st = a.done + (uint64_t)a.gid[t] * kR + r0;
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      live[k] = st[k] != 2;
+      any |= live[k];
+    }
+    if (!any) return false;
+    const uint32_t beg = a.rowT[t] + a.hc[i] * a.hub_chunk;
+    gather(t, beg, min(a.rowT[t + 1], beg + a.hub_chunk), r0, acc);
+    return true;
+  };
+  auto add = [&](uint32_t t, const bool(&live)[W], const float(&acc)[W]) {
+    float* dst = a.dv + (uint64_t)t * kR + r0;
+    if (a.rowT[t + 1] - a.rowT[t] <= a.hub_piece) {
+      float d[W];
+      vload<W>(dst, d);
+#pragma unroll
+      for (int k = 0; k < W; ++k)
+        if (live[k]) d[k] += acc[k];
+      vstore<W>(dst, d);
+    } else {
+#pragma unroll
+      for (int k = 0; k < W; ++k)
+        if (live[k] && acc[k] != 0.0f) unsafeAtomicAdd(dst + k, acc[k]);
+    }
+  };
+  if (a.hub_chunk == a.hub_piece) {  // pieces of one row
+    for (uint64_t base = i0 + (uint64_t)blockIdx.x * IPB; base < i1; base += (uint64_t)gridDim.x * IPB) {
+      const uint64_t i = base + sub;
+      bool live[W];
+      float acc[W];
+      if (i < i1 && chunk(i, live, acc)) add(a.ht[i], live, acc);
+    }
+    return;
+  }
+  __shared__ float s_acc[kHubRows][kR];
+  constexpr int kPasses = kHubRows / IPB;
+  const uint32_t per = a.hub_piece / a.hub_chunk;  // rows of a whole piece
+  for (uint64_t base = i0 + (uint64_t)blockIdx.x * kHubRows; base < i1; base += (uint64_t)gridDim.x * kHubRows) {
+    bool live[kPasses][W], on[kPasses];
+#pragma unroll
+    for (int q = 0; q < kPasses; ++q) {
+      const uint32_t row = q * IPB + sub;
+      float acc[W];
+      on[q] = chunk(base + row, live[q], acc);
+      vstore<W>(&s_acc[row][r0], acc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPasses; ++q) {
+      const uint32_t row = q * IPB + sub, c = a.hc[base + row];
+      if (!on[q] || c % per) continue;
+      const uint32_t t = a.ht[base + row];
+      const uint32_t rows = min(per, (a.rowT[t + 1] - a.rowT[t] + a.hub_chunk - 1) / a.hub_chunk - c);
+      float sum[W];
+      vload<W>(&s_acc[row][r0], sum);
+      for (uint32_t u = 1; u < rows; ++u) {
+        float x[W];
+        vload<W>(&s_acc[row + u][r0], x);
+#pragma unroll
+        for (int k = 0; k < W; ++k) sum[k] += x[k];
+      }
+      add(t, live[q], sum);
+    }
+    __syncthreads();
+  }
+}
+
 template <int LPV, bool WGT, bool SWEEP>
 __global__ __launch_bounds__(256) void k_bhub(BArgs a, int final_pass) {
   constexpr int W = kR / LPV;
-  constexpr int IPB = 256 / LPV;
   BCtl* ctl = a.ctl;
   const float *mu_in, *mu_prev = nullptr;
   uint64_t i0 = 0, i1 = a.n_hub;
@@ -588,41 +679,10 @@ __global__ __launch_bounds__(256) void k_bhub(BArgs a, int final_pass) {
     if (!final_pass && (bhalted(ctl) || ctl->mode != 2)) return;
     mu_in = mu_of_round(a, ctl->rounds - 1);
   }
-  const uint32_t sub = threadIdx.x / LPV;
-  const uint32_t r0 = (threadIdx.x % LPV) * W;
-  for (uint64_t base = i0 + (uint64_t)blockIdx.x * IPB; base < i1; base += (uint64_t)gridDim.x * IPB) {
-    const uint64_t i = base + sub;
-    if (i >= i1) continue;
-    const uint32_t t = a.ht[i];
-    const uint8_t* st = a.done + (uint64_t)a.gid[t] * kR + r0;
-    bool live[W], any = false;
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      live[k] = st[k] != 2;
-      any |= live[k];
-    }
-    if (!any) continue;
-    const uint32_t beg = a.rowT[t] + a.hc[i] * a.hub_chunk;
-    const uint32_t end = min(a.rowT[t + 1], beg + a.hub_chunk);
-    float acc[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) acc[k] = 0.0f;
+  hub_items<LPV>(a, i0, i1, [&](uint32_t, uint32_t beg, uint32_t end, uint32_t r0, float(&acc)[W]) {
     if constexpr (SWEEP) bgather_sweep<W, WGT>(a, mu_in, mu_prev, lo, prev_ok, beg, end, r0, acc);
     else bgather<W, WGT>(a, mu_in, beg, end, r0, acc);
-    float* dst = a.dv + (uint64_t)t * kR + r0;
-    if (a.rowT[t + 1] - a.rowT[t] <= a.hub_chunk) {
-      float d[W];
-      vload<W>(dst, d);
-#pragma unroll
-      for (int k = 0; k < W; ++k)
-        if (live[k]) d[k] += acc[k];
-      vstore<W>(dst, d);
-    } else {
-#pragma unroll
-      for (int k = 0; k < W; ++k)
-        if (live[k] && acc[k] != 0.0f) unsafeAtomicAdd(dst + k, acc[k]);
-    }
-  }
+  });
 }
 
 // Fused dense round, one block per residual item (a vertex range inside one
@@ -862,35 +922,16 @@ __global__ __launch_bounds__(256) void k_bdeliver(BArgs a) {
 template <int LPV, bool WGT>
 __global__ __launch_bounds__(256) void k_bdeliver_hub(BArgs a) {
   constexpr int W = kR / LPV;
-  constexpr int IPB = 256 / LPV;
   const BCtl* ctl = a.ctl;
   const uint64_t k = ctl->sw_k;
   const uint32_t cl = ctl->sw_c;
   const uint32_t L = (uint32_t)a.sw_bstart[cl + 1];
   const float* cur = (k & 1) ? a.mu2 : a.mu;
   const float* prev = (k & 1) ? a.mu : a.mu2;
-  const uint32_t sub = threadIdx.x / LPV;
-  const uint32_t r0 = (threadIdx.x % LPV) * W;
-  for (uint64_t base = (uint64_t)blockIdx.x * IPB; base < a.n_hub; base += (uint64_t)gridDim.x * IPB) {
-    const uint64_t i = base + sub;
-    if (i >= a.n_hub) continue;
-    const uint32_t t = a.ht[i];
+  hub_items<LPV>(a, 0, a.n_hub, [&](uint32_t t, uint32_t beg, uint32_t end, uint32_t r0, float(&acc)[W]) {
     const uint32_t bt = a.sw_blk[t];
     const uint32_t T0 = (uint32_t)a.sw_bstart[bt];
     const bool processed = bt <= cl;
-    const uint8_t* stp = a.done + (uint64_t)a.gid[t] * kR + r0;
-    bool live[W], any = false;
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-      live[q] = stp[q] != 2;
-      any |= live[q];
-    }
-    if (!any) continue;
-    const uint32_t beg = a.rowT[t] + a.hc[i] * a.hub_chunk;
-    const uint32_t end = min(a.rowT[t + 1], beg + a.hub_chunk);
-    float acc[W];
-#pragma unroll
-    for (int q = 0; q < W; ++q) acc[q] = 0.0f;
     for (uint32_t p = beg; p < end; ++p) {
       const uint32_t sp = a.srcT[p];
       const float* src = nullptr;
@@ -907,11 +948,7 @@ __global__ __launch_bounds__(256) void k_bdeliver_hub(BArgs a) {
 #pragma unroll
       for (int q = 0; q < W; ++q) acc[q] += x[q] * wp;
     }
-    float* dst = a.dv + (uint64_t)t * kR + r0;
-#pragma unroll
-    for (int q = 0; q < W; ++q)
-      if (live[q] && acc[q] != 0.0f) unsafeAtomicAdd(dst + q, acc[q]);
-  }
+  });
 }
 
 // After a delivery: back to a sparse state whose residual pass (count 0)
@@ -1185,6 +1222,51 @@ static void enqueue_push(daic_batch* b, hipStream_t s) {
   else hipLaunchKernelGGL(k_bpush<64>, dim3(g), dim3(256), 0, s, b->a);
 }
 
+// The rows (target, chunk) of the hub targets, appended to ht and hc. Pieces
+// of one row: longest first, so that the long ones start early. Pieces of
+// several rows: in bundles of kHubRows, the largest piece first and the rest
+// filled with the largest that fit (rows left over have no target).
+static void hub_table(const std::vector<uint32_t>& targets, const std::vector<uint32_t>& rt, uint32_t chunk,
+                      uint32_t piece, std::vector<uint32_t>& ht, std::vector<uint32_t>& hc) {
+  struct Piece {
+    uint32_t len, t, c;  // in-edges, target, first chunk
+  };
+  std::vector<Piece> pieces;
+  for (uint32_t t : targets) {
+    const uint32_t deg = rt[t + 1] - rt[t];
+    for (uint32_t e = 0; e < deg; e += piece) pieces.push_back({std::min(piece, deg - e), t, e / chunk});
+  }
+  std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.len > y.len; });
+  auto put = [&](uint32_t t, uint32_t c) {
+    ht.push_back(t);
+    hc.push_back(c);
+  };
+  if (chunk == piece) {
+    for (const Piece& p : pieces) put(p.t, p.c);
+    return;
+  }
+  std::vector<Piece> by_rows[kHubRows + 1];
+  for (auto p = pieces.rbegin(); p != pieces.rend(); ++p) by_rows[(p->len + chunk - 1) / chunk].push_back(*p);
+  uint32_t most = kHubRows;
+  for (;;) {
+    while (most && by_rows[most].empty()) --most;
+    if (!most) return;
+    uint32_t left = kHubRows;
+    for (uint32_t k = most; k; k = std::min(k, left)) {
+      if (by_rows[k].empty()) {
+        --k;
+        if (!k) break;
+        continue;
+      }
+      const Piece p = by_rows[k].back();
+      by_rows[k].pop_back();
+      for (uint32_t u = 0; u < k; ++u) put(p.t, p.c + u);
+      left -= k;
+    }
+    for (; left; --left) put(kNoRow, 0);
+  }
+}
+
 // One round in whichever mode the control block holds: sparse (claim, push,
 // residual), the claim that opens the dense phase, or a fused dense round.
 // Sweep set-up for P blocks per graph: graph g's block c is its vertices
@@ -1304,19 +1386,11 @@ static daic_status batch_sweep_setup(daic_batch* b, uint32_t P, hipStream_t s) {
   // hub items grouped by block, longest first
   std::vector<uint32_t> ht, hc, hoff(P + 1, 0);
   {
-    std::vector<std::vector<std::pair<uint32_t, uint64_t>>> per(P);
-    for (uint64_t t = 0; t < N; ++t) {
-      const uint32_t deg = rt[t + 1] - rt[t];
-      if (deg <= a.hub_deg) continue;
-      for (uint32_t c = 0; c * hub_chunk < deg; ++c)
-        per[blk[t]].push_back({std::min(hub_chunk, deg - c * hub_chunk), (t << 32) | c});
-    }
+    std::vector<std::vector<uint32_t>> per(P);
+    for (uint64_t t = 0; t < N; ++t)
+      if (rt[t + 1] - rt[t] > a.hub_deg) per[blk[t]].push_back((uint32_t)t);
     for (uint32_t c = 0; c < P; ++c) {
-      std::stable_sort(per[c].begin(), per[c].end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-      for (auto& it : per[c]) {
-        ht.push_back((uint32_t)(it.second >> 32));
-        hc.push_back((uint32_t)it.second);
-      }
+      hub_table(per[c], rt, hub_chunk, kSwHubChunk, ht, hc);
       hoff[c + 1] = (uint32_t)ht.size();
     }
   }
@@ -1353,6 +1427,7 @@ static daic_status batch_sweep_setup(daic_batch* b, uint32_t P, hipStream_t s) {
   as.n_res = (uint32_t)nres;
   as.n_hub = ht.size();
   as.hub_chunk = hub_chunk;
+  as.hub_piece = kSwHubChunk;
   as.sw_P = P;
   {
     uint32_t* d_inv = nullptr;
@@ -1540,21 +1615,11 @@ daic_status daic_batch_create(uint32_t n_graphs, const daic_graph* const* graphs
       a.hub_chunk = kHubChunkMin;  // a power of two; 16 chunks to a workgroup
       while (a.hub_chunk < kBChunk && hub / a.hub_chunk > 16 * kItemsWanted) a.hub_chunk *= 2;
     }
-    std::vector<uint32_t> ht, hc;
-    {
-      std::vector<std::pair<uint32_t, uint64_t>> items;  // (length, target << 32 | chunk)
-      for (uint64_t t = 0; t < N; ++t) {
-        const uint32_t deg = rt[t + 1] - rt[t];
-        if (deg <= a.hub_deg) continue;
-        for (uint32_t c = 0; c * a.hub_chunk < deg; ++c)
-          items.push_back({std::min(a.hub_chunk, deg - c * a.hub_chunk), (t << 32) | c});
-      }
-      std::stable_sort(items.begin(), items.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-      for (auto& it : items) {
-        ht.push_back((uint32_t)(it.second >> 32));
-        hc.push_back((uint32_t)it.second);
-      }
-    }
+    a.hub_piece = kBChunk;
+    std::vector<uint32_t> hubs, ht, hc;
+    for (uint64_t t = 0; t < N; ++t)
+      if (rt[t + 1] - rt[t] > a.hub_deg) hubs.push_back((uint32_t)t);
+    hub_table(hubs, rt, a.hub_chunk, a.hub_piece, ht, hc);
     a.n_hub = ht.size();
     BGRAB(ht, const uint32_t*, ht.size() * 4);
     BGRAB(hc, const uint32_t*, hc.size() * 4);
