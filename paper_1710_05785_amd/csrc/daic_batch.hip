@@ -1978,11 +1978,6 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
   // to that many rounds is a single graph launch
   constexpr uint32_t kBatchLaunchRounds = 128;
   const uint32_t K = o->rounds_per_check ? o->rounds_per_check : kBatchLaunchRounds;
-  // the rounds until the host sees the dense phase launch the kernels of
-  // every mode; the dense phase then has a graph of its own, without the four
-  // that would return at once (4-5 us each)
-  constexpr uint32_t kBatchOpenRounds = 8;
-  const uint32_t K_open = std::min(K, kBatchOpenRounds);
   const uint64_t max_rounds = o->max_rounds ? o->max_rounds : ~0ull;
   if (stats) std::memset(stats, 0, sizeof *stats);
   BArgs& a = b->a;
@@ -2009,18 +2004,12 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
     if (b->graph_f) { (void)hipGraphDestroy(b->graph_f); b->graph_f = nullptr; }
     b->exec_K = 0;  // no match until every capture below has succeeded
     DAIC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    for (uint32_t r = 0; r < K_open; ++r) enqueue_round(b, s);
+    for (uint32_t r = 0; r < K; ++r) enqueue_round(b, s);
     hipGraph_t graph;
     DAIC_HIP(hipStreamEndCapture(s, &graph));
     b->graph = graph;
     DAIC_HIP(hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0));
-    if (!sweep) {
-      DAIC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-      for (uint32_t r = 0; r < K; ++r) enqueue_dense(b, s, 0);
-      DAIC_HIP(hipStreamEndCapture(s, &graph));
-      b->graph_f = graph;
-      DAIC_HIP(hipGraphInstantiate(&b->exec_f, graph, nullptr, nullptr, 0));
-    } else {
+    if (sweep) {
       DAIC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
       for (uint32_t r = 0; r < K; ++r) enqueue_sweep(b, s);
       DAIC_HIP(hipStreamEndCapture(s, &graph));
@@ -2037,6 +2026,16 @@ daic_status daic_batch_run(daic_batch* b, const daic_run_opts* o, daic_stats* st
   DAIC_HIP(hipStreamSynchronize(s));
   for (;;) {
     const bool sweep_now = sweep && b->h_ctl->mode == 3, dense_now = b->h_ctl->mode == 2;
+    // once the host has seen the dense phase, its rounds take a graph without
+    // the five kernels of the other modes, which would return at once (18 us a round)
+    if (use_graph && dense_now && !b->exec_f) {
+      hipGraph_t graph;
+      DAIC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+      for (uint32_t r = 0; r < K; ++r) enqueue_dense(b, s, 0);
+      DAIC_HIP(hipStreamEndCapture(s, &graph));
+      b->graph_f = graph;
+      DAIC_HIP(hipGraphInstantiate(&b->exec_f, graph, nullptr, nullptr, 0));
+    }
     if (use_graph) {
       DAIC_HIP(hipGraphLaunch(sweep_now ? b->exec_sw : dense_now ? b->exec_f : b->exec, s));
     } else {
