@@ -131,7 +131,9 @@ struct SmallWalk {
     for (int i = 0; i < 4; ++i) {
       if constexpr (Tr<ST>::sum) {
         double x = (double)m[i];
-        if constexpr (G == DAIC_G_EDGE_SCALE) x *= (double)y.x[i];
+        // (a silent sender sends nothing, whatever its weight: an infinite one
+        // times 0 would be a NaN)
+        if constexpr (G == DAIC_G_EDGE_SCALE) x *= m[i] != (S)0 ? (double)y.x[i] : 0.0;
         small_add<ST>(acc, x);
       } else {
         small_add<ST>(acc, tile_mm_msg<ST, G>(m[i], y.x + i, 0));
