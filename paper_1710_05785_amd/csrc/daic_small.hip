@@ -178,6 +178,11 @@ __device__ __forceinline__ void small_receive(typename SmallAcc<ST>::L acc, type
   using S = typename Tr<ST>::S;
   if constexpr (Tr<ST>::sum) {
     if (acc != 0.0) dv = (S)((double)dv + acc);
+  } else if constexpr (ST == ST_F64MIN) {
+    // compared as doubles: messages are not negative, but a starting distance
+    // may be, and its bits are above every message's
+    const double x = TileMM<ST>::dec(acc);
+    if (x < v && x < dv) dv = x;
   } else {
     if (TileMM<ST>::better(acc, TileMM<ST>::enc(v)) && TileMM<ST>::better(acc, TileMM<ST>::enc(dv)))
       dv = (S)TileMM<ST>::dec(acc);

@@ -3,6 +3,8 @@ workgroup."""
 import numpy as np
 import pytest
 
+import daic_gen
+
 pytestmark = pytest.mark.gpu
 
 daic = pytest.importorskip("paper_1710_05785_amd.daic")
@@ -33,3 +35,29 @@ def test_small_runs_send_nothing_over_silent_edges(weight, state):
         ref[3:23] = 0.25 ** np.arange(20)
         np.testing.assert_allclose(v[:23], ref[:23], rtol=1e-6, atol=0, err_msg=sched)
         assert np.isfinite(v).all(), sched
+
+
+def test_small_runs_keep_distances_below_zero():
+    """Starting distances may be negative (weights may not): a message that is
+    no smaller than a pending one leaves it."""
+    n = 4000
+    src = np.concatenate([[0], np.arange(n)])
+    dst = np.concatenate([[n - 1], (np.arange(n) * 7 + 1) % n])
+    g = daic_gen.from_edges(n, src, dst)
+    w = np.full(g.m, 5.0)
+    p = daic.Problem(daic.Graph(g.row_ptr, g.col, w), daic.MIN, daic.G_EDGE_ADD, state="f64")
+    v0 = np.full(n, np.inf)
+    dv = v0.copy()
+    dv[0], dv[n - 1] = 0.0, -3.0
+    row, col = g.row_ptr.astype(np.int64), g.col.astype(np.int64)
+    ref, tail = dv.copy(), np.repeat(np.arange(n), np.diff(row))
+    for _ in range(n):
+        new = ref.copy()
+        np.minimum.at(new, col, ref[tail] + 5.0)
+        if np.array_equal(new, ref):
+            break
+        ref = new
+    for sched in ("exact", "all"):
+        p.set_init(v0, dv)
+        assert p.run(sched=sched, q=1.0 / n if sched == "exact" else 1.0).converged
+        np.testing.assert_array_equal(p.get(), ref, err_msg=sched)
