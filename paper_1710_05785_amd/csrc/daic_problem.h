@@ -154,9 +154,11 @@ void apply_run_opts(daic_problem* p, const daic_run_opts* o);
 void clear_radix(daic_problem* p, hipStream_t s);
 // Fourth condition of Sec. 3.1 on the current state (needs the constant c).
 daic_status check_init(daic_problem* p, double tol, uint64_t* mismatches, hipStream_t s);
-// Runs of small problems: whether a run takes the one-workgroup form, and the
-// run itself (the control block's mirror h_ctl holds the result).
+// Runs of small problems: whether a run takes the one-workgroup form, the
+// layout that a problem's first such run builds, and the run itself (the
+// control block's mirror h_ctl holds the result).
 bool small_applies(const daic_problem* p, const daic_run_opts* o);
+daic_status small_prepare(daic_problem* p, hipStream_t s);
 daic_status small_run(daic_problem* p, const daic_run_opts* o, hipStream_t s);
 void small_release(daic_problem* p);
 // SWEEP scheduling: the run loop, and the release of its per-problem state.

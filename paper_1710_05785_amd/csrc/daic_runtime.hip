@@ -1105,6 +1105,8 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
   }
   if (o->sched == DAIC_SCHED_SWEEP) return sweep_run(p, o, stats, s);
   if (small_applies(p, o)) {
+    rc = small_prepare(p, s);
+    if (rc) return rc;
     DAIC_HIP(hipEventRecord(p->ev0, s));
     rc = small_run(p, o, s);
     if (rc) return rc;

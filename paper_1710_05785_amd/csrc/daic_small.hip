@@ -730,12 +730,10 @@ bool small_applies(const daic_problem* p, const daic_run_opts* o) {
   return true;
 }
 
+daic_status small_prepare(daic_problem* p, hipStream_t s) { return p->small ? DAIC_OK : small_setup(p, s); }
+
 daic_status small_run(daic_problem* p, const daic_run_opts* o, hipStream_t s) {
   const uint32_t n = (uint32_t)p->g->dev.n;
-  if (!p->small) {
-    const daic_status rc = small_setup(p, s);
-    if (rc) return rc;
-  }
   SmallArgs t = *p->small;
   t.eps = o->eps;
   t.max_rounds = o->max_rounds ? o->max_rounds : ~0ull;
