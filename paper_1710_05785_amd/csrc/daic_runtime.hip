@@ -1229,20 +1229,38 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
   return run_stats(p, learned, stats);
 }
 
+// Whether a kernel on the device that holds `own` may read S-byte elements at
+// q: aligned memory of the same device. (Other memory, which a copy takes as
+// well, goes by copies: another device's or a host array would fault a kernel.)
+static bool readable_by(const void* own, const void* q, size_t S) {
+  hipPointerAttribute_t a{}, b{};
+  if (reinterpret_cast<uintptr_t>(q) % S) return false;
+  if (hipPointerGetAttributes(&a, own) != hipSuccess || hipPointerGetAttributes(&b, q) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return b.type == hipMemoryTypeDevice && a.device == b.device;
+}
+
 daic_status daic_problem_set_init_device(daic_problem* p, const void* d_v0, const void* d_dv1, void* hip_stream) {
   if (!p || !d_v0 || !d_dv1) return fail(DAIC_E_INVALID, "null argument");
   const uint64_t n = p->g->dev.n;
   if (n == 0) return DAIC_OK;
   hipStream_t s = hip_stream ? static_cast<hipStream_t>(hip_stream) : p->own_stream;
   const size_t S = state_size(p->st);
-  if (S == 8)
+  if (!readable_by(p->a.v, d_v0, S) || !readable_by(p->a.v, d_dv1, S)) {
+    DAIC_HIP(hipMemcpyAsync(p->a.v, d_v0, n * S, hipMemcpyDefault, s));
+    DAIC_HIP(hipMemcpyAsync(p->a.dv, d_dv1, n * S, hipMemcpyDefault, s));
+    if (p->a.c) hipLaunchKernelGGL(k_fill<float>, dim3(grid_for(n)), dim3(256), 0, s, p->a.c, 0.0f, n);
+  } else if (S == 8) {
     hipLaunchKernelGGL(k_set_state<uint64_t>, dim3(grid_for(n)), dim3(256), 0, s, static_cast<const uint64_t*>(d_v0),
                        static_cast<const uint64_t*>(d_dv1), n, static_cast<uint64_t*>(p->a.v),
                        static_cast<uint64_t*>(p->a.dv), p->a.c);
-  else
+  } else {
     hipLaunchKernelGGL(k_set_state<uint32_t>, dim3(grid_for(n)), dim3(256), 0, s, static_cast<const uint32_t*>(d_v0),
                        static_cast<const uint32_t*>(d_dv1), n, static_cast<uint32_t*>(p->a.v),
                        static_cast<uint32_t*>(p->a.dv), p->a.c);
+  }
   DAIC_HIP(hipGetLastError());
   if (!hip_stream) DAIC_HIP(hipStreamSynchronize(s));
   return DAIC_OK;
