@@ -1029,20 +1029,20 @@ daic_status daic_problem_set_init(daic_problem* p, const void* v0, const void* d
   if (n == 0) return DAIC_OK;
   DAIC_HIP(hipDeviceSynchronize());
   hipStream_t s = p->own_stream;
-  auto put = [&](const void* from, void* to, float* c) {
+  auto put = [&](const void* from, void* to, float* c) -> daic_status {
     void* host = const_cast<void*>(from);
     if (p->st == ST_F32 || p->st == ST_F32K)  // the compensation term carries the FP32 rounding of v0
       return stage_move<false>(host, n, 8, s, [&](const void* chunk, uint64_t first, uint64_t k) {
         hipLaunchKernelGGL((k_stage_in<double, float>), stage_grid(k), dim3(256), 0, s,
                            static_cast<const double*>(chunk), first, k, static_cast<float*>(to), c);
       });
-    if (state_size(p->st) == 8)
-      return stage_move<false>(host, n, 8, s, [&](const void* chunk, uint64_t first, uint64_t k) {
-        hipLaunchKernelGGL((k_stage_in<uint64_t, uint64_t>), stage_grid(k), dim3(256), 0, s,
-                           static_cast<const uint64_t*>(chunk), first, k, static_cast<uint64_t*>(to),
-                           static_cast<uint64_t*>(nullptr));
-      });
-    return stage_move<false>(host, n, 4, s, [&](const void* chunk, uint64_t first, uint64_t k) {
+    // the state's own element type
+    const size_t bytes = n * state_size(p->st);
+    if (bytes > kStageSmallWrite && bytes <= kStageLargeWrite) {
+      DAIC_HIP(hipMemcpy(to, from, bytes, hipMemcpyHostToDevice));
+      return DAIC_OK;
+    }
+    return stage_move<false>(host, bytes / 4, 4, s, [&](const void* chunk, uint64_t first, uint64_t k) {
       hipLaunchKernelGGL((k_stage_in<uint32_t, uint32_t>), stage_grid(k), dim3(256), 0, s,
                          static_cast<const uint32_t*>(chunk), first, k, static_cast<uint32_t*>(to),
                          static_cast<uint32_t*>(nullptr));
@@ -1573,13 +1573,8 @@ daic_status daic_problem_get(const daic_problem* p, void* v_out, void* dv_out) {
         hipLaunchKernelGGL((k_stage_out<float, double>), stage_grid(k), dim3(256), 0, s,
                            static_cast<const float*>(from), c, first, k, static_cast<double*>(chunk));
       });
-    if (state_size(p->st) == 8)
-      return stage_move<true>(host, n, 8, s, [&](void* chunk, uint64_t first, uint64_t k) {
-        hipLaunchKernelGGL((k_stage_out<uint64_t, uint64_t>), stage_grid(k), dim3(256), 0, s,
-                           static_cast<const uint64_t*>(from), static_cast<const uint64_t*>(nullptr), first, k,
-                           static_cast<uint64_t*>(chunk));
-      });
-    return stage_move<true>(host, n, 4, s, [&](void* chunk, uint64_t first, uint64_t k) {
+    const size_t bytes = n * state_size(p->st);
+    return stage_move<true>(host, bytes / 4, 4, s, [&](void* chunk, uint64_t first, uint64_t k) {
       hipLaunchKernelGGL((k_stage_out<uint32_t, uint32_t>), stage_grid(k), dim3(256), 0, s,
                          static_cast<const uint32_t*>(from), static_cast<const uint32_t*>(nullptr), first, k,
                          static_cast<uint32_t*>(chunk));

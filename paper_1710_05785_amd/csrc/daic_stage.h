@@ -29,6 +29,12 @@ namespace daic {
 constexpr size_t kStageChunk = 1u << 20;   // bytes of a chunk
 constexpr uint32_t kStageThreads = 8;      // host threads of a transfer at most
 constexpr uint32_t kStageBuffers = 2;      // chunks of each in turn
+// Arrays of these sizes that need no conversion are written by a plain copy:
+// each of v and dv with 64 KiB of doubles 12 us, 16 through the chunks; 1 MiB
+// 42 and 52; 8 MiB 240 and 285; 16 MiB 515 and 515; 32 MiB 1,050 and 910. 4 KiB
+// take 14 us either way, but the first kernel after such a copy 9 more. (Reads
+// are faster through the chunks: 4 KiB 15 us against 30, 4 MiB 190 against 260.)
+constexpr size_t kStageSmallWrite = 16u << 10, kStageLargeWrite = 12u << 20;
 
 // The process's pinned buffers: one chunk, and with the first larger transfer
 // kStageThreads x kStageBuffers of them (16 MiB). They exist while problems

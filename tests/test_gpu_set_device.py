@@ -1,12 +1,13 @@
-"""daic_problem_set_init_device takes what a copy takes: aligned arrays of the
+"""Where initial values come from. daic_problem_set_init_device takes what a copy takes: aligned arrays of the
 state's device (read by a kernel), and arrays at odd addresses, in pinned and
-in ordinary host memory (copied)."""
+in ordinary host memory (copied); daic_problem_set_init takes host arrays by a
+plain copy from 16 KiB to 12 MiB and through pinned chunks otherwise."""
 import ctypes
 
 import numpy as np
 import pytest
 
-from test_gpu_transfer import empty_graph, weighted_graph
+from test_gpu_transfer import empty_graph, roundtrip, weighted_graph
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +49,10 @@ def test_arrays_of_any_memory(state, where):
     np.testing.assert_array_equal(got_v, v.astype(got_v.dtype))
     np.testing.assert_array_equal(got_dv, dv.astype(got_dv.dtype))
     del keep_a, keep_b
+
+
+@pytest.mark.parametrize("state", ["f64", "u32"])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_host_arrays_around_the_limits_of_plain_copies(state, more):
+    for limit in (16 << 10, 12 << 20):
+        assert roundtrip(limit // (8 if state == "f64" else 4) + more, state)
