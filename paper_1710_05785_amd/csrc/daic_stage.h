@@ -18,7 +18,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -36,13 +35,18 @@ constexpr uint32_t kStageBuffers = 2;      // chunks of each in turn
 // are faster through the chunks: 4 KiB 15 us against 30, 4 MiB 190 against 260.)
 constexpr size_t kStageSmallWrite = 16u << 10, kStageLargeWrite = 12u << 20;
 
-// The process's pinned buffers: one chunk, and with the first larger transfer
-// kStageThreads x kStageBuffers of them (16 MiB). They exist while problems
-// or batches do (their StageUser) and serve one transfer at a time.
-// Takes the buffers for a transfer of `chunks` chunks (waits for another
-// transfer to end); null when pinned memory is not to be had.
-char* stage_lock(uint64_t chunks);
-void stage_unlock();
+// The process's pinned buffers, in blocks: one chunk, and kStageBuffers for
+// each of two or of kStageThreads threads (16 MiB; 30 us to allocate, 0.1 ms to
+// free; as sixteen of 1 MiB 0.5 and 2 ms). They exist while problems or batches
+// do (their StageUser); kStageKept of each size are kept between transfers. A
+// transfer holds a block of its own and waits for no other (a lock held during
+// transfers had a read of 8 KB take 5.3 ms beside reads of 268 MB that took
+// 6.3); beyond those kept, it allocates and frees one.
+// stage_take returns null when pinned memory is not to be had.
+constexpr uint32_t kStageKept = 2;
+constexpr uint32_t kStageBlocks[3] = {1, 2 * kStageBuffers, kStageThreads * kStageBuffers};  // chunks
+char* stage_take(uint32_t size);
+void stage_give(char* block, uint32_t size);
 
 // One thread's share of a transfer: chunks t, t + T, ...
 template <bool OUT, typename Enqueue>
@@ -99,7 +103,10 @@ daic_status stage_move(void* host, uint64_t count, size_t elem, hipStream_t s, c
   if (count == 0) return DAIC_OK;
   char* h = static_cast<char*>(host);
   const uint64_t per = kStageChunk / elem, chunks = (count + per - 1) / per;
-  char* buf = stage_lock(chunks);
+  const uint32_t T = (uint32_t)std::max<uint64_t>(  // threads
+      1, std::min<uint64_t>({kStageThreads, std::max(1u, std::thread::hardware_concurrency()), chunks / 2}));
+  const uint32_t size = chunks == 1 ? 0 : T <= 2 ? 1 : 2;
+  char* buf = stage_take(size);
   hipError_t e = hipSuccess;
   if (!buf) {  // no pinned memory: a device chunk and plain copies
     void* d = nullptr;
@@ -120,8 +127,6 @@ daic_status stage_move(void* host, uint64_t count, size_t elem, hipStream_t s, c
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (OUT && e == hipSuccess) std::memcpy(h, buf, count * elem);
   } else {
-    const uint32_t T = (uint32_t)std::min<uint64_t>(
-        {kStageThreads, std::max(1u, std::thread::hardware_concurrency()), chunks / 2});
     int device = 0;
     e = hipGetDevice(&device);
     hipError_t got[kStageThreads] = {};
@@ -135,7 +140,7 @@ daic_status stage_move(void* host, uint64_t count, size_t elem, hipStream_t s, c
     for (uint32_t t = 1; t < T && e == hipSuccess; ++t) {
       try {
         pool[t] = std::thread(share, t);
-      } catch (const std::system_error&) {
+      } catch (...) {
         mine[t] = true;  // no thread to be had: its share after this thread's own
       }
     }
@@ -145,7 +150,7 @@ daic_status stage_move(void* host, uint64_t count, size_t elem, hipStream_t s, c
       if (pool[t].joinable()) pool[t].join();
     for (uint32_t t = 0; t < T && e == hipSuccess; ++t) e = got[t];
   }
-  if (buf) stage_unlock();
+  if (buf) stage_give(buf, size);
   if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? DAIC_E_OOM : DAIC_E_DEVICE, "host transfer: %s", hipGetErrorString(e));
   return DAIC_OK;

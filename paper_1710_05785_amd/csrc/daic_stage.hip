@@ -6,42 +6,52 @@
 namespace daic {
 
 namespace {
-std::mutex g_life;      // users and the allocations
-std::mutex g_transfer;  // held during a transfer
+struct Blocks {  // those not in use
+  char* block[kStageKept];
+  uint32_t count = 0;
+};
+std::mutex g_lock;
 uint32_t g_users = 0;
-char* g_one = nullptr;  // one chunk
-char* g_all = nullptr;  // kStageThreads x kStageBuffers chunks
+Blocks g_blocks[3];  // of each size
 }  // namespace
 
 StageUser::StageUser() {
-  std::lock_guard<std::mutex> l(g_life);
+  std::lock_guard<std::mutex> l(g_lock);
   ++g_users;
 }
 
+// (Transfers are made with a handle, so every block is back.)
 StageUser::~StageUser() {
-  std::lock_guard<std::mutex> l(g_life);
+  std::lock_guard<std::mutex> l(g_lock);
   if (--g_users) return;
-  if (g_one) (void)hipHostFree(g_one);
-  if (g_all) (void)hipHostFree(g_all);
-  g_one = g_all = nullptr;
+  for (Blocks& b : g_blocks)
+    while (b.count) (void)hipHostFree(b.block[--b.count]);
 }
 
-// The caller holds a handle, so the buffers stay until it is done.
-char* stage_lock(uint64_t chunks) {
-  g_transfer.lock();
-  char** p = chunks > 1 ? &g_all : &g_one;
+char* stage_take(uint32_t size) {
   {
-    std::lock_guard<std::mutex> l(g_life);
-    const size_t bytes = kStageChunk * (chunks > 1 ? kStageThreads * kStageBuffers : 1);
-    if (!*p && hipHostMalloc((void**)p, bytes, hipHostMallocPortable) != hipSuccess) {
-      (void)hipGetLastError();
-      *p = nullptr;
+    std::lock_guard<std::mutex> l(g_lock);
+    Blocks& b = g_blocks[size];
+    if (b.count) return b.block[--b.count];
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kStageChunk * kStageBlocks[size], hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return static_cast<char*>(p);
+}
+
+void stage_give(char* block, uint32_t size) {
+  {
+    std::lock_guard<std::mutex> l(g_lock);
+    Blocks& b = g_blocks[size];
+    if (b.count < kStageKept) {
+      b.block[b.count++] = block;
+      return;
     }
   }
-  if (!*p) g_transfer.unlock();
-  return *p;
+  (void)hipHostFree(block);
 }
-
-void stage_unlock() { g_transfer.unlock(); }
 
 }  // namespace daic
