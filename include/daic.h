@@ -202,8 +202,8 @@ daic_status daic_problem_set_init_device(daic_problem* p, const void* d_v0, cons
  * tile and the partition width 2^bits; the sweep schedule's tiles take
  * DAIC_SWEEP_TILE_EDGES, DAIC_SWEEP_TILE_BITS and DAIC_SWEEP_TILE_SHARE,
  * the divisor of a block's in-edges that sizes its tiles). Runs of ALL,
- * TOPK_EXACT, TOPK_SAMPLED and ROUND_ROBIN on small graphs (n <= 16,384 and
- * up to 2^18 edges) stay in one workgroup from the first round to the stop
+ * TOPK_EXACT, TOPK_SAMPLED and ROUND_ROBIN on small graphs (n <= 16,384, for
+ * some types and rules from 8,192 on less, and up to 2^18 edges) stay in one workgroup from the first round to the stop
  * rule, unless DAIC_NO_SMALL=1 or one of the settings above that picks a form
  * of the per-round kernels is given. Every form
  * ends in the same state after the same rounds (min/max bit for bit, sums up

@@ -41,9 +41,9 @@ constexpr uint32_t kSmallPiece = 32;         // in-edges of a piece: vertices wi
 constexpr uint32_t kSmallMaxHeavy = 2048;    // vertices cut into pieces at most
 constexpr uint32_t kSmallDegs = 768;         // distinct out-degrees (k of them take k (k - 1) / 2 edges)
 constexpr uint32_t kSmallMaxN = 16384;       // message bases of 8 bytes each: 128 of the CU's 160 KiB
-constexpr uint32_t kSmallMaxM = 1u << 18;    // in-edges at most (see small_applies)
-constexpr uint64_t kSmallStream = 3u << 19;  // bytes of in-neighbours and weights per round at most, for
-                                             // rules whose general rounds have no threshold kernels
+constexpr uint32_t kSmallMaxM = 1u << 18;    // in-edges at most: as many as were measured (see small_most_rows)
+constexpr uint32_t kSmallMinEdges = 1u << 17;  // and of FP64 shortest paths (see small_most_rows),
+constexpr uint32_t kSmallMinRows = 12;         // which take at most this many rows
 constexpr uint32_t kSmallRounds = 4096;      // rounds per launch at most
 
 struct SmallArgs {
@@ -675,21 +675,16 @@ daic_status small_setup(daic_problem* p, hipStream_t s) {
   return DAIC_OK;
 }
 
-template <int ST, int G>
+// The kernel of the smallest even number of rows (vertices per thread) that
+// holds the vertices: two rows too many cost 0.4 to 3 us of a round (5,000
+// vertices in 6 and 8 rows: FP64 PageRank 6.8 and 7.1 us, FP64 SSSP 14.3 and
+// 16.3; 13,000 in 14 and 16: 16.6 and 22.2, 42 and 46).
+template <int ST, int G, int NPT = 2>
 void small_launch(daic_problem* p, const SmallArgs& t, hipStream_t s) {
-  const uint32_t rows = ((uint32_t)p->g->dev.n + kSmallThreads - 1) / kSmallThreads;
-  if (rows <= 2)
-    hipLaunchKernelGGL((k_small_run<ST, G, 2>), dim3(1), dim3(kSmallThreads), 0, s, p->a, t);
-  else if (rows <= 4)
-    hipLaunchKernelGGL((k_small_run<ST, G, 4>), dim3(1), dim3(kSmallThreads), 0, s, p->a, t);
-  else if (rows <= 8)
-    hipLaunchKernelGGL((k_small_run<ST, G, 8>), dim3(1), dim3(kSmallThreads), 0, s, p->a, t);
-  else if (rows <= 10)
-    hipLaunchKernelGGL((k_small_run<ST, G, 10>), dim3(1), dim3(kSmallThreads), 0, s, p->a, t);
-  else if (rows <= 12)
-    hipLaunchKernelGGL((k_small_run<ST, G, 12>), dim3(1), dim3(kSmallThreads), 0, s, p->a, t);
-  else
-    hipLaunchKernelGGL((k_small_run<ST, G, 16>), dim3(1), dim3(kSmallThreads), 0, s, p->a, t);
+  if constexpr (NPT < (int)(ST == ST_F64MIN ? kSmallMinRows : kSmallMaxN / kSmallThreads)) {
+    if (p->g->dev.n > (uint64_t)NPT * kSmallThreads) return small_launch<ST, G, NPT + 2>(p, t, s);
+  }
+  hipLaunchKernelGGL((k_small_run<ST, G, NPT>), dim3(1), dim3(kSmallThreads), 0, s, p->a, t);
 }
 
 template <int ST>
@@ -701,27 +696,66 @@ void small_launch_sum(daic_problem* p, const SmallArgs& t, hipStream_t s) {
 
 }  // namespace
 
-// One CU against the whole chip's round kernels, us per round (this form /
-// the general one), power-law graphs, MI355X:
-//                        PageRank FP32+K   PageRank FP64   Adsorption FP64   SSSP u32
-//   all,    n = 1,025      4.1 / 17          4.5 / 19        6.0 / 20          7 / 41
-//           n = 4,096      6.2 / 24          6.6 / 26        9.5 / 28         10 / 41
-//           n = 9,999     11 / 23           11 / 24         24 / 28           16 / 45
-//           n = 16,384    19 / 25           24 / 27         39 / 29           25 / 46
-//   exact,  n = 9,999     20 / 76           20 / 114        32 / 117          24 / 73
-//           n = 16,384    32 / 77           38 / 117        53 / 118          37 / 80
-//   sampled n = 9,999     17 / 57           17 / 56         30 / 60           23 / 63
-// A round's time follows the bytes it streams (2 per in-edge, and the
-// weight): up to 1.5 MiB it is below the general rounds of every rule, beyond
-// that only below the rules with a threshold.
+// The most rows (1,024 vertices each) that run in one workgroup, by kind of
+// problem and rule: where one CU stops being faster than the chip's round
+// kernels. It loses to them as its time grows with the in-edges, and with the
+// rows, whose state leaves the registers for scratch memory (from 8 or 10 rows
+// of 8-byte values on). us per round, this form / the round kernels, at the
+// last size of a row of the table and beyond it, on a power-law graph of 11.7
+// in-edges per vertex and an RMAT graph of 16:
+//                                     ALL               ROUND_ROBIN       sampled           exact
+//   PageRank FP32+K    n = 16,384   19 / 21, 25 / 23  21 / 28, 24 / 29  26 / 35, 31 / 36  33 / 44, 37 / 46
+//   PageRank FP64      n = 14,336   18 / 22, 24 / 25  20 / 27, 24 / 31  26 / 36, 34 / 41  31 / 59, 39 / 65
+//                      n = 16,384   24 / 21, 30 / 24  27 / 29, 31 / 31  34 / 38, 42 / 40  41 / 61, 48 / 65
+//   Adsorption FP32    n = 14,336   21 / 23, 26 / 26  22 / 28, 27 / 32  29 / 35, 34 / 39  34 / 43, 38 / 47
+//                      n = 16,384   26 / 22, 31 / 24  28 / 30, 32 / 31  33 / 37, 38 / 38  40 / 44, 44 / 46
+//   Adsorption FP32+K  n = 12,288   21 / 21, 26 / 25  22 / 27, 26 / 31  29 / 34, 33 / 38  33 / 42, 36 / 46
+//                      n = 14,336   25 / 23, 30 / 26  27 / 27, 31 / 32  32 / 34, 37 / 39  37 / 42, 41 / 47
+//   Adsorption FP64    n =  8,192   19 / 24, 22 / 25  19 / 28, 23 / 33  26 / 36, 30 / 40  27 / 60, 30 / 64
+//                      n = 10,240   25 / 24, 29 / 26  25 / 28, 29 / 33  31 / 36, 36 / 41  34 / 59, 38 / 63
+//                      n = 12,288   30 / 24, 34 / 27  31 / 29, 36 / 33  37 / 37, 42 / 42  41 / 60, 45 / 64
+//                      n = 14,336   35 / 25, 41 / 27  37 / 29, 42 / 33  42 / 38, 48 / 42  48 / 60, 53 / 65
+//   SSSP u32           n = 16,384   24 / 34, 29 / 35  25 / 31, 28 / 29  29 / 40, 35 / 41  36 / 51, 38 / 51
+//   SSSP FP64          n = 10,240   26 / 34, 34 / 34  25 / 30, 31 / 27  33 / 41, 39 / 43  41 / 63, 46 / 59
+//                      n = 12,288   36 / 33, 45 / 37  35 / 31, 43 / 28  43 / 40, 51 / 44  54 / 64, 61 / 60
+//                      n = 14,336   46 / 32, 52 / 31  46 / 31, 49 / 28  54 / 40, 58 / 45  73 / 65, 72 / 60
+// (2^18 edges on 1,025 vertices: PageRank FP32+K 21 / 119, Adsorption FP64 28 / 120,
+// SSSP FP64 30 / 80.) FP64 shortest paths by round-robin, and all pending beyond
+// eight rows, also need few edges: a round sends along a fraction of them, which
+// the round kernels push and this form walks whole (8,192 vertices, ROUND_ROBIN:
+// 131,072 edges 23 / 27, 262,144 36 / 28).
+static uint32_t small_most_rows(const daic_problem* p, daic_sched sched) {
+  enum { U32_I32, SUM_F32, SUM_F64, WSUM_F32, WSUM_F32K, WSUM_F64, MIN_F64 };
+  static constexpr uint32_t rows[7][4] = {
+      // ALL, ROUND_ROBIN, sampled, exact
+      {16, 16, 16, 16},  // U32_I32
+      {16, 16, 16, 16},  // SUM_F32
+      {14, 16, 16, 16},  // SUM_F64
+      {14, 16, 16, 16},  // WSUM_F32
+      {12, 16, 16, 16},  // WSUM_F32K
+      {8, 10, 12, 16},   // WSUM_F64
+      {10, 10, 10, kSmallMinRows},  // MIN_F64
+  };
+  const bool weighted = p->gk == DAIC_G_EDGE_SCALE;
+  const int kind = p->st == ST_F64MIN ? MIN_F64
+                   : p->st == ST_U32 || p->st == ST_I32 ? U32_I32
+                   : p->st == ST_F64 ? (weighted ? WSUM_F64 : SUM_F64)
+                   : !weighted ? SUM_F32 : p->st == ST_F32 ? WSUM_F32 : WSUM_F32K;
+  switch (sched) {
+    case DAIC_SCHED_ALL: return rows[kind][0];
+    case DAIC_SCHED_ROUND_ROBIN: return rows[kind][1];
+    case DAIC_SCHED_TOPK_SAMPLED: return rows[kind][2];
+    case DAIC_SCHED_TOPK_EXACT: return rows[kind][3];
+    default: return 0;
+  }
+}
+
 bool small_applies(const daic_problem* p, const daic_run_opts* o) {
   const GraphDev& d = p->g->dev;
-  if (d.n > kSmallMaxN || d.m > kSmallMaxM || !d.row32) return false;
-  const bool topk = o->sched == DAIC_SCHED_TOPK_EXACT || o->sched == DAIC_SCHED_TOPK_SAMPLED;
-  if (!topk && o->sched != DAIC_SCHED_ALL && o->sched != DAIC_SCHED_ROUND_ROBIN) return false;
-  uint64_t per_edge = 2;
-  if (p->gk == DAIC_G_EDGE_SCALE || p->gk == DAIC_G_EDGE_ADD) per_edge += p->st == ST_F64 || p->st == ST_F64MIN ? 8 : 4;
-  if (!topk && d.m * per_edge > kSmallStream) return false;
+  if (d.m > kSmallMaxM || !d.row32) return false;
+  if (d.n > (uint64_t)small_most_rows(p, o->sched) * kSmallThreads) return false;
+  const bool whole = o->sched == DAIC_SCHED_ROUND_ROBIN || (o->sched == DAIC_SCHED_ALL && d.n > 8 * kSmallThreads);
+  if (p->st == ST_F64MIN && whole && d.m > kSmallMinEdges) return false;
   // a setting that asks for one form of the per-round kernels gets it
   for (const char* e : {"DAIC_NO_SMALL", "DAIC_NO_GRAPH", "DAIC_NO_FUSE", "DAIC_NO_PULL", "DAIC_NO_TILE",
                         "DAIC_PULL_DIV", "DAIC_PULL_EDGE_DIV", "DAIC_TILE_EDGES", "DAIC_TILE_BITS",

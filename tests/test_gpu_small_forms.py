@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import daic_gen
+from test_gpu_small import CASES, test_small_runs_match_round_kernels as match_round_kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +81,11 @@ def test_time_of_a_first_small_run():
         p.set_init(np.zeros(g.n), np.full(g.n, 0.2))
         times.append((first, p.run(sched="all", max_rounds=3).stats["time_ms"]))
     assert min(a for a, _ in times) <= 2 * max(b for _, b in times), times
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(c))
+@pytest.mark.parametrize("n", [6144, 6145, 8192, 10240, 12288, 14336, 14337])
+def test_small_runs_at_the_rows_of_their_kernels(case, n, monkeypatch):
+    """The last size that each even number of rows of 1,024 holds, and the
+    sizes at which some rules go to the round kernels."""
+    match_round_kernels(case, n, monkeypatch)
