@@ -93,6 +93,7 @@ struct daic_problem {
   float* score = nullptr;        // selection multiplier of each vertex
   daic::SweepState* sweep = nullptr;
   daic::SmallArgs* small = nullptr;  // whole runs in one workgroup: the layout (built on first use)
+  bool small_off = false;            // the problem's weights keep it from them
   void* cst = nullptr;           // constant c of the update function (fourth-condition check), or null
 };
 
@@ -155,8 +156,9 @@ void clear_radix(daic_problem* p, hipStream_t s);
 // Fourth condition of Sec. 3.1 on the current state (needs the constant c).
 daic_status check_init(daic_problem* p, double tol, uint64_t* mismatches, hipStream_t s);
 // Runs of small problems: whether a run takes the one-workgroup form, the
-// layout that a problem's first such run builds, and the run itself (the
-// control block's mirror h_ctl holds the result).
+// layout that a problem's first such run builds (none, and small_off, when its
+// weights turn out to keep it from the form), and the run itself (the control
+// block's mirror h_ctl holds the result).
 bool small_applies(const daic_problem* p, const daic_run_opts* o);
 daic_status small_prepare(daic_problem* p, hipStream_t s);
 daic_status small_run(daic_problem* p, const daic_run_opts* o, hipStream_t s);

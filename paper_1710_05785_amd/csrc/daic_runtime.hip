@@ -1104,9 +1104,13 @@ daic_status daic_run(daic_problem* p, const daic_run_opts* o, daic_stats* stats)
     if (rc) return rc;
   }
   if (o->sched == DAIC_SCHED_SWEEP) return sweep_run(p, o, stats, s);
-  if (small_applies(p, o)) {
+  bool small = small_applies(p, o);
+  if (small) {
     rc = small_prepare(p, s);
     if (rc) return rc;
+    small = !p->small_off;
+  }
+  if (small) {
     DAIC_HIP(hipEventRecord(p->ev0, s));
     rc = small_run(p, o, s);
     if (rc) return rc;

@@ -131,9 +131,7 @@ struct SmallWalk {
     for (int i = 0; i < 4; ++i) {
       if constexpr (Tr<ST>::sum) {
         double x = (double)m[i];
-        // (a silent sender sends nothing, whatever its weight: an infinite one
-        // times 0 would be a NaN)
-        if constexpr (G == DAIC_G_EDGE_SCALE) x *= m[i] != (S)0 ? (double)y.x[i] : 0.0;
+        if constexpr (G == DAIC_G_EDGE_SCALE) x *= (double)y.x[i];  // 0 of a silent sender: weights are finite
         small_add<ST>(acc, x);
       } else {
         small_add<ST>(acc, tile_mm_msg<ST, G>(m[i], y.x + i, 0));
@@ -475,6 +473,16 @@ __global__ void k_small_weights(const S* w, const uint32_t* eid, uint64_t count,
     out[i] = eid[i] == 0xFFFFFFFFu ? (S)0 : w[eid[i]];
 }
 
+// *found = 1 when a weight (the bits of a float or a double) is infinite or NaN.
+template <typename S>
+__global__ void k_small_nonfinite(const S* w, uint64_t m, uint64_t* found) {
+  constexpr S kExp = sizeof(S) == 8 ? (S)0x7FF0000000000000ull : (S)0x7F800000u;
+  bool any = false;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (uint64_t)gridDim.x * blockDim.x)
+    any |= (w[i] & kExp) == kExp;
+  if (any) *found = 1;
+}
+
 namespace {
 
 // The layout of k_small_run, computed on the host (a millisecond at most for
@@ -592,6 +600,27 @@ daic_status small_setup(daic_problem* p, hipStream_t s) {
   const uint32_t n = (uint32_t)d.n, m = (uint32_t)d.m;
   const size_t S = p->st == ST_F64 || p->st == ST_F64MIN ? 8 : 4;
   const bool weighted = p->gk == DAIC_G_EDGE_SCALE || p->gk == DAIC_G_EDGE_ADD;
+  if (p->gk == DAIC_G_EDGE_SCALE && m) {
+    // A weight that is no number must reach its target only when its sender
+    // sends. The round kernels' pushes skip silent senders; here each in-edge
+    // adds base x weight, and a select per in-edge to keep a silent 0 apart
+    // took 0.2 to 1 us of a round's 5 to 33, so such graphs keep those kernels.
+    uint64_t found = 0;  // (part_n: partials of the residual, free between rounds)
+    DAIC_HIP(hipMemsetAsync(p->a.part_n, 0, 8, s));
+    const dim3 grid((uint32_t)std::min<uint64_t>(256, m / 256 + 1));
+    if (S == 8)
+      hipLaunchKernelGGL(k_small_nonfinite<uint64_t>, grid, dim3(256), 0, s, static_cast<const uint64_t*>(p->a.w),
+                         (uint64_t)m, p->a.part_n);
+    else
+      hipLaunchKernelGGL(k_small_nonfinite<uint32_t>, grid, dim3(256), 0, s, static_cast<const uint32_t*>(p->a.w),
+                         (uint64_t)m, p->a.part_n);
+    DAIC_HIP(hipMemcpyAsync(&found, p->a.part_n, 8, hipMemcpyDeviceToHost, s));
+    DAIC_HIP(hipStreamSynchronize(s));
+    if (found) {
+      p->small_off = true;
+      return DAIC_OK;
+    }
+  }
   std::vector<uint32_t> row(n + 1), col(m);
   DAIC_HIP(hipMemcpyAsync(row.data(), d.row, (n + 1) * 4ull, hipMemcpyDeviceToHost, s));
   if (m) DAIC_HIP(hipMemcpyAsync(col.data(), d.col, m * 4ull, hipMemcpyDeviceToHost, s));
@@ -752,7 +781,7 @@ static uint32_t small_most_rows(const daic_problem* p, daic_sched sched) {
 
 bool small_applies(const daic_problem* p, const daic_run_opts* o) {
   const GraphDev& d = p->g->dev;
-  if (d.m > kSmallMaxM || !d.row32) return false;
+  if (d.m > kSmallMaxM || !d.row32 || p->small_off) return false;
   if (d.n > (uint64_t)small_most_rows(p, o->sched) * kSmallThreads) return false;
   const bool whole = o->sched == DAIC_SCHED_ROUND_ROBIN || (o->sched == DAIC_SCHED_ALL && d.n > 8 * kSmallThreads);
   if (p->st == ST_F64MIN && whole && d.m > kSmallMinEdges) return false;

@@ -103,9 +103,7 @@ daic_status stage_move(void* host, uint64_t count, size_t elem, hipStream_t s, c
   if (count == 0) return DAIC_OK;
   char* h = static_cast<char*>(host);
   const uint64_t per = kStageChunk / elem, chunks = (count + per - 1) / per;
-  const uint32_t T = (uint32_t)std::max<uint64_t>(  // threads
-      1, std::min<uint64_t>({kStageThreads, std::max(1u, std::thread::hardware_concurrency()), chunks / 2}));
-  const uint32_t size = chunks == 1 ? 0 : T <= 2 ? 1 : 2;
+  const uint32_t size = chunks == 1 ? 0 : chunks / 2 <= 2 ? 1 : 2;
   char* buf = stage_take(size);
   hipError_t e = hipSuccess;
   if (!buf) {  // no pinned memory: a device chunk and plain copies
@@ -127,6 +125,8 @@ daic_status stage_move(void* host, uint64_t count, size_t elem, hipStream_t s, c
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (OUT && e == hipSuccess) std::memcpy(h, buf, count * elem);
   } else {
+    const uint32_t T = (uint32_t)std::min<uint64_t>(
+        {kStageThreads, std::max(1u, std::thread::hardware_concurrency()), chunks / 2});
     int device = 0;
     e = hipGetDevice(&device);
     hipError_t got[kStageThreads] = {};
