@@ -463,7 +463,9 @@ daic_status daic_run_progress(daic_problem* p, const daic_run_opts* opts, uint64
  * reports per kernel class: launches, summed duration and the algorithmic
  * bytes those launches had to move (per-edge and per-vertex figures of the
  * round's actual work). At most cap classes are written; *n_out receives
- * the count. Slower than daic_run (one host sync per round).             */
+ * the count. Slower than daic_run (one host sync per round). It always takes
+ * the per-round kernels: for the small graphs that daic_run keeps in one
+ * workgroup it times the rounds that DAIC_NO_SMALL=1 would run.            */
 typedef struct {
   char name[32];
   uint64_t launches;

@@ -31,7 +31,7 @@ __device__ __forceinline__ T wave_sum(T x) {
   return x;
 }
 
-// Exclusive block scan of up to three counters at once; returns the block
+// Exclusive block scan of NV counters at once; returns the block
 // totals through tot[]. Every thread of the block must call it.
 template <int NV>
 __device__ __forceinline__ void block_excl_scan(uint32_t (&x)[NV], uint32_t (&tot)[NV]) {

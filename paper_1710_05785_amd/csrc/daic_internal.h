@@ -70,7 +70,6 @@ struct Ctl {
   uint32_t l_run;        // learned rounds since the last exact round
   uint32_t l_pad;
   double l_r0;           // residual at the start of the round
-  uint64_t l_rounds0;    // round count at the start of the round
   double l_gain;         // priority realized by the round's updates (sum over the selected vertices)
   double l_exact_eff;    // the judge's figure for the last exact round
   uint64_t l_fallbacks;  // learned rounds that handed the next rounds back to exact selection

@@ -13,7 +13,8 @@
 //                             and max problems) or, without them, k_pull_stream
 //                             (sum problems; then k_pull_finish: residual and
 //                             stop rule)
-//   A1 k_residual + k_residual_final : residual of the new state and the stop rule
+//   A1 k_settle + k_total   : residual of the new state and the stop rule (rounds
+//                             with tiles; k_residual + k_residual_final without)
 // Fused dense rounds (every pending vertex, sum problems): the tiled kernels
 // with FUSED = true, or k_pull_fused + k_fused_finish, per round after one
 // priming claim.
@@ -390,7 +391,6 @@ __device__ __forceinline__ void topk_begin(Ctl* ctl, uint64_t pending, uint64_t 
 // are owed).
 __device__ __forceinline__ void learned_pre(Ctl* ctl) {
   ctl->l_r0 = ctl->r;
-  ctl->l_rounds0 = ctl->rounds;
   ctl->use_score = ctl->l_exact_left == 0 ? 1u : 0u;
 }
 
@@ -751,7 +751,6 @@ static __global__ void k_init_ctl(Ctl* ctl, double eps, uint64_t max_rounds) {
   ctl->l_exact_left = 1;  // a learned run starts with one exact round (the judge's calibration)
   ctl->l_run = 0;
   ctl->l_r0 = 0.0;
-  ctl->l_rounds0 = 0;
   ctl->l_gain = 0.0;
   ctl->l_exact_eff = 0.0;
   ctl->l_fallbacks = 0;

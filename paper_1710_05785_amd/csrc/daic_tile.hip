@@ -311,7 +311,9 @@ static void tile_shape(const daic_graph* g, uint32_t* lb_out, uint64_t* max_edge
   // 104.1 -> 103.1, components on 262,144 vertices 32.8 -> 30.4, SSSP on
   // RMAT-20 102.6 -> 92.3; 0.75 of the average and 1.25 were slower). From
   // 2^12 targets on a split partition's finish is dearer: RMAT-22 in f64
-  // took 193 us at two averages, 212 at one
+  // took 193 us at two averages, 212 at one. The floor of 16,384 in-edges is
+  // the default's (300,000-vertex adsorption, whose partitions average 7,700:
+  // 37.3 us with it, 36.4 with 8,192, no more than its runs differ by)
   const uint64_t n_part = std::max<uint64_t>(1, (n + (1ull << lb) - 1) >> lb);
   const uint64_t least = lb <= 11 ? std::max<uint64_t>(16384, std::min<uint64_t>(kTileE, m / n_part)) : tile_default_edges(n, m, lb);
   uint64_t max_edges = std::max<uint64_t>(least, m / ((uint64_t)std::max(cus, 1) * tile_wgs_per_cu(lb)));
